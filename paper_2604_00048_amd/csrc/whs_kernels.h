@@ -73,3 +73,11 @@ bool chunk_path(const LaunchDesc& L);
 hipError_t launch_chunk(const LaunchDesc& L, bool bwd, hipStream_t stream);
 
 }  // namespace whs
+
+namespace whs {
+
+// several segments per series (small batches, one band, order <= 2): see whs_seg.hip
+bool seg_path(const LaunchDesc& L);
+hipError_t launch_seg(const LaunchDesc& L, bool bwd, hipStream_t stream);
+
+}  // namespace whs
