@@ -24,7 +24,8 @@
 //
 // A workgroup holds SW series x nseg segments (lane = segment * SW + series):
 // SW = 64 gives whole rows per wavefront, smaller SW more segments per series.
-// NT = SW * nseg work-items, one wavefront per SIMD.
+// NT = SW * nseg work-items, one wavefront per SIMD.  MB: a group of C bands of
+// a call that has more.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,7 +47,7 @@ struct SegArgs {
 template <int D, int C>
 constexpr int seg_fields() { return ck_fields<D, C>() + D * D; }
 
-template <int D, int C, int B, typename TS, bool BWD, bool PERDIFF, bool WB, int NT>
+template <int D, int C, int B, typename TS, bool BWD, bool PERDIFF, bool WB, int NT, bool MB = false>
 struct Seg {
   static constexpr int NF = seg_fields<D, C>();
   static constexpr int NY = D * (D + 1) / 2;
@@ -69,10 +70,10 @@ struct Seg {
   // wave-uniform
   __amdgpu_buffer_rsrc_t rx, rw, rl, rz, ro, rg, rck;
   int T, tps;
-  // blocks of 64 series: bytes between two bands of a row, and per row of x
-  // (all bands), of lambda, of w and of one checkpoint field
-  static constexpr uint32_t Sb = 64u * ES, Rx = (uint32_t)C * Sb, Rl = Sb, Rw = WB ? 8u : 64u,
-                            ckrow = NT * 8u;
+  uint32_t Rx;  // bytes per row of x, all bands (a constant for one band alone)
+  // blocks of 64 series: bytes between two bands of a row, and per row of
+  // lambda, of w and of one checkpoint field
+  static constexpr uint32_t Sb = 64u * ES, Rl = Sb, Rw = WB ? 8u : 64u, ckrow = NT * 8u;
   // per lane
   uint32_t lx, ll, lw, lc, bit;
   int r0;               // first row of the segment
@@ -557,17 +558,19 @@ struct Seg {
     const int64_t p = p0 + s_wg;
     T = a.T;
     tps = g.tps;
+    const int ctot = C == 1 && !MB ? 1 : a.Ctot;
+    Rx = C == 1 && !MB ? Sb : (uint32_t)a.Ctot * Sb;
     accum = a.glam_accum != 0;
     const uint32_t xbytes = (uint32_t)T * Rx, lbytes = (uint32_t)(T - D) * Rl;
-    rx = make_rsrc(static_cast<const TS*>(a.rhs) + bidx * T * C * 64, xbytes);
+    rx = make_rsrc(static_cast<const TS*>(a.rhs) + bidx * T * ctot * 64, xbytes);
     rw = make_rsrc(a.w + bidx * T * (int64_t)Rw, (uint32_t)T * Rw);
     rl = make_rsrc(PERDIFF ? (const void*)(static_cast<const TS*>(a.lam) + bidx * (T - D) * 64) : (const void*)a.w,
                    PERDIFF ? lbytes : 0u);
     const bool out = a.out != nullptr, grad = BWD && a.glam != nullptr;
-    ro = make_rsrc(out ? (const void*)(static_cast<TS*>(a.out) + bidx * T * C * 64) : (const void*)a.w,
+    ro = make_rsrc(out ? (const void*)(static_cast<TS*>(a.out) + bidx * T * ctot * 64) : (const void*)a.w,
                    out ? xbytes : 0u);
     if constexpr (BWD) {
-      rz = make_rsrc(static_cast<const TS*>(a.zin) + bidx * T * C * 64, grad ? xbytes : 0u);
+      rz = make_rsrc(static_cast<const TS*>(a.zin) + bidx * T * ctot * 64, grad ? xbytes : 0u);
       rg = make_rsrc(grad && PERDIFF ? (const void*)(static_cast<TS*>(a.glam) + bidx * (T - D) * 64) : (const void*)a.w,
                      grad && PERDIFF ? lbytes : 0u);
     }
@@ -575,7 +578,7 @@ struct Seg {
     rck = make_rsrc(a.ck + (int64_t)wg * (ckbytes / 8), ckbytes);
     const bool live = p < a.P && seg < g.ne;
     const uint32_t l0 = (uint32_t)s_in * ES;
-    lx = live ? l0 : kDead;
+    lx = live ? l0 + (MB ? (uint32_t)a.c0 * Sb : 0u) : kDead;
     ll = live ? l0 : kDead;
     lw = live ? (WB ? ((uint32_t)s_in >> 5) << 2 : (uint32_t)s_in) : kDead;
     bit = (uint32_t)s_in & 31u;
@@ -724,9 +727,9 @@ struct Seg {
   }
 };
 
-template <int D, int C, int B, typename TS, bool BWD, bool PERDIFF, bool WB, int NT>
+template <int D, int C, int B, typename TS, bool BWD, bool PERDIFF, bool WB, int NT, bool MB = false>
 __global__ __launch_bounds__(NT, 1) void k_seg(SegArgs g) {
-  using K = Seg<D, C, B, TS, BWD, PERDIFF, WB, NT>;
+  using K = Seg<D, C, B, TS, BWD, PERDIFF, WB, NT, MB>;
   __shared__ double xs[K::NX * NT];
   __shared__ int nobs[NT];
   __shared__ int flag[NT];

@@ -1,6 +1,5 @@
 """GPU parity of the segmented solve and adjoint (batches of up to 32,768
-series of at least 512 steps, one band, order 1 or 2, FP32 storage, interleave
-64) against the oracle.  Eliminating the segments' interiors before their
+series of at least 512 steps, order 1 or 2, FP32 storage, interleave 64) against the oracle.  Eliminating the segments' interiors before their
 separators is Cholesky of a symmetric permutation of Omega, so the results are
 held to the bar of the sequential sweep: 1e-4 per series for FP32 storage (or
 the bound of the result's own backward error), componentwise backward error
@@ -46,7 +45,7 @@ def _check(x, w, lam, d, P, rows=slice(None)):
     if gl.ndim == 1:
         # a sum of signed terms over days: against the summed magnitudes
         u, _ = R.solve_band_rhs(g[ok], w[ok], lam[ok], d)
-        size = np.abs(R.apply_D(u[:, :, 0], d) * R.apply_D(zc[ok][:, :, 0], d)).sum(1)
+        size = sum(np.abs(R.apply_D(u[:, :, c], d) * R.apply_D(zc[ok][:, :, c], d)).sum(1) for c in range(u.shape[2]))
         el = np.abs(gl[ok] - gl_ref) / size
     else:
         el = np.abs(gl[ok] - gl_ref).max(1) / np.abs(gl_ref).max(1)
@@ -66,6 +65,14 @@ def test_fewer_segments_for_more_series(P, T, d):
     # 16, 8, 4 and 2 segments; the oracle checks the first and last series and some between
     x, w, lam = random_case(P, T, d, per_diff=True, seed=P + T, dtype=torch.float32, p_obs=0.1)
     _check(x, w, lam, d, P, rows=np.r_[0:3, P // 2:P // 2 + 3, P - 3:P])
+
+
+@pytest.mark.parametrize("P,T,d,C,per_diff", [(70, 900, 2, 2, False), (5, 1300, 2, 7, True), (9, 700, 1, 3, True),
+                                              (66, 640, 1, 4, False)])
+def test_band_groups(P, T, d, C, per_diff):
+    # solve in groups of 3, 2 and 1 bands, adjoint in groups of 2 and 1
+    x, w, lam = random_case(P, T, d, C=C, per_diff=per_diff, seed=P + T + C, dtype=torch.float32, p_obs=0.1)
+    _check(x, w, lam, d, P)
 
 
 def test_failures_are_reported_like_the_sequential_sweep():
