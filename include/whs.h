@@ -119,11 +119,14 @@ size_t whs_workspace_bytes(const whs_desc* desc);
  * interleaved layout with a tiled transpose, run the throughput kernels and
  * copy the results back: about two more passes over the data, for every order
  * and band count, and the uneven-date calls then accept interleave 1 too.
+ * One band of d <= 2 in FP32, at least 512 steps long on the daily grid, reads
+ * and writes the contiguous arrays directly instead, several segments per
+ * series, with the same results.
  * With less (but at least whs_workspace_bytes), interleave-1 calls run the
- * kernels that read the contiguous layout in place: for one band and d <= 2
- * the partition kernel (256 lanes per series, for P < 2^24), which is the
- * faster choice for small batches (below about 10,000 series of 3288 steps,
- * where one lane per series leaves most of the GPU idle). */
+ * kernels that read the contiguous layout in place: the same segments where
+ * the workspace holds their checkpoints and P > 1024, else for one band and
+ * d <= 2 the partition kernel (256 lanes per series, for P < 2^24), the faster
+ * choice for the smallest batches. */
 size_t whs_interleave_workspace_bytes(const whs_desc* desc);
 
 /* Bytes of the factor array whs_factor writes: P_pad * (d+1) * T * 8. */

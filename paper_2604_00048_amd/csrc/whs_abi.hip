@@ -286,8 +286,6 @@ int whs_solve(const whs_desc* desc, const uint8_t* w, const void* lambda, const 
       !aligned(info, 4))
     return WHS_ERR_ARG;
   if (!workspace || workspace_bytes < whs_workspace_bytes(desc) || !aligned(workspace, 8)) return WHS_ERR_WORKSPACE;
-  if (use_staged(desc, factor, workspace_bytes))
-    return hip_status(solve_staged(desc, nullptr, w, lambda, x, z, info, workspace, static_cast<hipStream_t>(stream)));
   whs::LaunchDesc L = make_launch(desc);
   L.w = w;
   L.lam = lambda;
@@ -296,6 +294,10 @@ int whs_solve(const whs_desc* desc, const uint8_t* w, const void* lambda, const 
   L.out = z;
   L.info = info;
   L.ws = static_cast<double*>(workspace);
+  L.ws_bytes = workspace_bytes;
+  L.in_place = !use_staged(desc, factor, workspace_bytes);
+  if (!L.in_place && !whs::seg_path(L, false))
+    return hip_status(solve_staged(desc, nullptr, w, lambda, x, z, info, workspace, static_cast<hipStream_t>(stream)));
   return hip_status(whs::launch_solve(L, static_cast<hipStream_t>(stream)));
 }
 
@@ -330,9 +332,6 @@ int whs_backward(const whs_desc* desc, const uint8_t* w, const void* lambda, con
     return WHS_ERR_ARG;
   if (!workspace || workspace_bytes < whs_workspace_bytes(desc) || !aligned(workspace, 8)) return WHS_ERR_WORKSPACE;
   if (!grad_x && !grad_lambda && !info) return WHS_OK;
-  if (use_staged(desc, factor, workspace_bytes))
-    return hip_status(backward_staged(desc, nullptr, w, lambda, z, g, grad_x, grad_lambda, info, workspace,
-                                      static_cast<hipStream_t>(stream)));
   whs::LaunchDesc L = make_launch(desc);
   L.w = w;
   L.lam = lambda;
@@ -343,6 +342,11 @@ int whs_backward(const whs_desc* desc, const uint8_t* w, const void* lambda, con
   L.glam = grad_lambda;
   L.info = info;
   L.ws = static_cast<double*>(workspace);
+  L.ws_bytes = workspace_bytes;
+  L.in_place = !use_staged(desc, factor, workspace_bytes);
+  if (!L.in_place && !whs::seg_path(L, true))
+    return hip_status(backward_staged(desc, nullptr, w, lambda, z, g, grad_x, grad_lambda, info, workspace,
+                                      static_cast<hipStream_t>(stream)));
   return hip_status(whs::launch_backward(L, static_cast<hipStream_t>(stream)));
 }
 

@@ -67,8 +67,8 @@ size_t checkpoint_bytes(int64_t P, int S, int T, int D, int C) {
 }
 
 hipError_t launch_solve(const LaunchDesc& L, hipStream_t stream) {
+  if (seg_path(L, false)) return launch_seg(L, false, stream);
   if (chunk_path(L)) return launch_chunk(L, false, stream);
-  if (seg_path(L)) return launch_seg(L, false, stream);
   if (L.coef) {
     switch (L.D) {
       case 1: return run_solve_tab_d1(L, stream);
@@ -88,8 +88,8 @@ hipError_t launch_solve(const LaunchDesc& L, hipStream_t stream) {
 }
 
 hipError_t launch_backward(const LaunchDesc& L, hipStream_t stream) {
+  if (seg_path(L, true)) return launch_seg(L, true, stream);
   if (chunk_path(L)) return launch_chunk(L, true, stream);
-  if (seg_path(L)) return launch_seg(L, true, stream);
   if (L.coef) {
     switch (L.D) {
       case 1: return run_backward_tab_d1(L, stream);

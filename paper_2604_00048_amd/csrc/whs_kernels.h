@@ -23,6 +23,8 @@ struct LaunchDesc {
   double* ws;         // checkpoint workspace
   const double* coef = nullptr;  // rows of D on uneven sample times, (T-D) x (D+1); null: daily grid
   bool wbits = false;            // w one bit per series (S a multiple of 64, fused path only)
+  size_t ws_bytes = 0;           // bytes of ws (series-contiguous calls)
+  bool in_place = false;         // a workspace too small for interleaved copies (series-contiguous calls)
 };
 
 size_t checkpoint_bytes(int64_t P, int S, int T, int D, int C);
@@ -76,8 +78,8 @@ hipError_t launch_chunk(const LaunchDesc& L, bool bwd, hipStream_t stream);
 
 namespace whs {
 
-// several segments per series (small batches, one band, order <= 2): see whs_seg.hip
-bool seg_path(const LaunchDesc& L);
+// several segments per series (small batches, order <= 2): see whs_seg.hip
+bool seg_path(const LaunchDesc& L, bool bwd);
 hipError_t launch_seg(const LaunchDesc& L, bool bwd, hipStream_t stream);
 
 }  // namespace whs

@@ -29,12 +29,11 @@ GRID = [10.0 ** (-1.0 + 0.3 * i) for i in range(21)]
 
 
 def layout_for(P: int) -> int:
-    """Interleave of a batch of P series.  Up to a few thousand series, one lane
-    per series leaves most of the chip idle and the smoother calls wait on the
-    sequential recurrence (about 0.64 ms for the solve of 4096 or of 16384 series
-    of 3288 days); series-contiguous tensors (interleave 1) take the partition
-    kernel instead, 256 lanes per series (0.26 ms for 4096), and the network's
-    input and head kernels read them coalesced."""
+    """Interleave of a batch of P series.  Up to a few thousand series the smoother
+    runs several segments per series in either layout (4096 series of 3288 days:
+    0.10 ms interleaved, 0.12 ms series-contiguous for the solve), and on
+    series-contiguous tensors (interleave 1) the network's input and head kernels
+    read coalesced."""
     return 1 if P <= SMALL_BATCH else S
 
 
@@ -105,12 +104,11 @@ class Learned:
 
     def train_step(self, batch: Batch, lr: float) -> float:
         h, lam = self.weights(batch, keep=True)
-        # series-contiguous batches: the in-place partition kernel (staged=False)
-        z, info = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P, staged=False)
+        z, info = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P)
         loss = torch.zeros(1, dtype=torch.float64, device=self.device)
         # MSE in standardised units: (z - x)^2 / sd^2 averaged over held-out points
         g = net.mse(z, batch.x_true, batch.hold, 1.0 / (max(batch.n_hold, 1) * self.sd ** 2), loss=loss)
-        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False, staged=False)
+        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False)
         gh = net.head_bwd1(h, glam, batch.P, T_DAYS, batch.S, D)
         self.model.backward1(gh, batch.P, T_DAYS)
         self.model.adam(lr)
@@ -133,10 +131,10 @@ class LearnedScalar:
 
     def train_step(self, batch: Batch, lr: float, sd: float) -> float:
         lam = self.weights(batch)
-        z, _ = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P, staged=False)
+        z, _ = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P)
         loss = torch.zeros(1, dtype=torch.float64, device=self.device)
         g = net.mse(z, batch.x_true, batch.hold, 1.0 / (max(batch.n_hold, 1) * sd ** 2), loss=loss)
-        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False, staged=False)
+        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False)
         gt = net.scalar_head_bwd(self.theta, glam, batch.P)
         self.step += 1
         net._chk(net.lib().whs_net_adam(net._p(self.theta), net._p(gt), net._p(self.m), net._p(self.v), 1, lr, 0.9,

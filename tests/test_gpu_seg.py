@@ -116,3 +116,44 @@ def test_partial_outputs_and_in_place():
     for a, b in ((z, xi), (gx, gx1), (gx, gi)):
         np.testing.assert_array_equal(from_device_series(a, P), from_device_series(b, P))
     np.testing.assert_array_equal(from_device_rows(gl, P), from_device_rows(gl1, P))
+
+
+def _at_offset(t, k):
+    """The values of t at a storage offset of k elements."""
+    buf = torch.zeros(t.numel() + k, dtype=t.dtype, device=t.device)
+    v = buf[k:].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("P,T,d,per_diff,k_x,k_w", [
+    (3, 512, 2, True, 0, 0), (70, 513, 2, True, 1, 1), (9, 1001, 1, False, 3, 2), (33, 770, 1, True, 0, 3),
+    (130, 3288, 2, False, 2, 0), (2100, 600, 2, True, 1, 3), (4099, 531, 1, True, 0, 1), (8200, 517, 2, False, 1, 2),
+    (16391, 523, 2, True, 3, 1),
+])
+def test_contiguous_arrays_match_interleaved_bit_for_bit(P, T, d, per_diff, k_x, k_w):
+    # the same segments on (P, T) arrays, rows and addresses of any alignment
+    x, w, lam = random_case(P, T, d, per_diff=per_diff, seed=P + T + d, dtype=torch.float32, p_obs=0.1)
+    if P > 4:
+        w[2] = 0           # a failed series
+    g = torch.tensor(np.random.default_rng(P).normal(size=x.shape), dtype=torch.float32)
+    x64, w64, l64 = to_device(x, w, lam, 64, torch.float32)
+    x1, w1, l1 = to_device(x, w, lam, 1, torch.float32)
+    x1, w1, l1 = _at_offset(x1, k_x), _at_offset(w1, k_w), _at_offset(l1, k_x)
+    g64, g1 = synth.pack_series(g, 64).cuda(), _at_offset(synth.pack_series(g, 1).cuda(), k_x)
+    z64, i64 = whs.whs_solve(x64, w64, l64, d, P)
+    gx64, gl64, _ = whs.whs_backward(w64, l64, z64, g64, d, P)
+    z1, i1 = whs.whs_solve(x1, w1, l1, d, P, z=_at_offset(torch.full_like(x1, 7.0), k_x))
+    gx1, gl1, j1 = whs.whs_backward(w1, l1, z1, g1, d, P, grad_x=_at_offset(torch.full_like(x1, 7.0), k_x),
+                                    grad_lambda=_at_offset(torch.full_like(l1, 7.0), k_x))
+    none, gl2, _ = whs.whs_backward(w1, l1, z1, g1, d, P, need_x=False)
+    gx2, none, _ = whs.whs_backward(w1, l1, z1, g1, d, P, need_lambda=False)
+    xi = x1.clone()
+    whs.whs_solve(xi, w1, l1, d, P, z=xi)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(i1.cpu().numpy(), i64.cpu().numpy())
+    np.testing.assert_array_equal(j1.cpu().numpy(), i64.cpu().numpy())
+    for a, b in ((z1, z64), (xi, z64), (gx1, gx64), (gx2, gx64)):
+        np.testing.assert_array_equal(from_device_series(a, P), from_device_series(b, P))
+    for a, b in ((gl1, gl64), (gl2, gl64)):
+        np.testing.assert_array_equal(from_device_rows(a, P), from_device_rows(b, P))
