@@ -119,7 +119,8 @@ size_t whs_workspace_bytes(const whs_desc* desc);
  * interleaved layout with a tiled transpose, run the throughput kernels and
  * copy the results back: about two more passes over the data, for every order
  * and band count, and the uneven-date calls then accept interleave 1 too.
- * One band of d <= 2 in FP32, at least 512 steps long on the daily grid, reads
+ * One band of d <= 2 in FP32, at least 96 steps long (512 for the solve with a
+ * weight per series) on the daily grid, reads
  * and writes the contiguous arrays directly instead, several segments per
  * series, with the same results.
  * With less (but at least whs_workspace_bytes), interleave-1 calls run the

@@ -11,14 +11,16 @@ hipError_t run_seg_backward_d1(const LaunchDesc&, hipStream_t);
 hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 
 // Where it runs: daily grid, FP32 storage, order <= 2, blocks of 64 series, at
-// least 512 steps, and a batch that one lane per series leaves waiting on its
+// least 96 steps (4 tiles), and a batch that one lane per series leaves waiting on its
 // own recurrence.  3288 steps, order 2, a weight per difference row, solve /
 // adjoint in us, one lane per series -> segments:
 //      512 series   620 /  815 ->  48 /  69      16,384 series  681 / 869 -> 287 / 417
 //    4,096 series   643 /  825 -> 103 / 153      32,768 series  722 / 914 -> 558 / 801
 // (from 4096 series on the segments run at the memory's rate, about 28 and 40
 // bytes per series-step at 5 TB/s, checkpoints included).  512 steps, 4,096
-// series: 105 / 143 -> 22 / 29.  Ten bands, 16,384 series of 3288 steps: solve
+// series: 105 / 143 -> 22 / 29; 150 steps: 41 / 55 -> 17 / 22, 32,768 series 45 /
+// 58 -> 35 / 47; at 64 steps, three tiles, 34 / 41 -> 27 / 30 on 4,096 series but
+// level on 65,536 contiguous ones.  Ten bands, 16,384 series of 3288 steps: solve
 // and adjoint 8.07 -> 4.11 ms.  At 65,536 series one lane per series already
 // fills every SIMD and moves fewer checkpoint bytes.
 // Series-contiguous arrays of one band take the same kernel, their row pieces
@@ -30,12 +32,13 @@ hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 // to 96 bytes split lines of 128, and the lines that 65,536 lanes hold open in
 // five arrays exceed the L2).
 // Not taken: FP64 storage, whose callers see the last digits, which another
-// order of elimination changes on ill-conditioned series; fewer than 512
-// steps, where a solve gives bit for bit what a plan's launch of one lane per
-// series gives; order 3 and 4, whose state leaves no registers for the spike.
+// order of elimination changes on ill-conditioned series; the one-band solve with
+// a weight per series below 512 steps, which gives bit for bit what a plan's
+// launch of one lane per series gives for that group; order 3 and 4, whose state leaves no registers for the spike.
 bool seg_path(const LaunchDesc& L, bool bwd) {
-  if (L.fac || L.coef || L.f64 || L.D > 2 || L.T < 512 || L.P < 1 || L.P >= ((int64_t)1 << 31))
+  if (L.fac || L.coef || L.f64 || L.D > 2 || L.T < 96 || L.P < 1 || L.P >= ((int64_t)1 << 31))
     return false;
+  if (L.T < 512 && !bwd && !L.perdiff && L.C == 1) return false;
   if (L.S != 64 && !(L.S == 1 && L.C == 1)) return false;
   if ((int64_t)L.T * L.C * 256 >= ((int64_t)1 << 30)) return false;  // 32-bit offsets, tiles past the end included
   SegShape s;

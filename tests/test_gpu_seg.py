@@ -1,6 +1,6 @@
 """GPU parity of the segmented solve and adjoint (batches of up to 32,768
-series of at least 512 steps, order 1 or 2, FP32 storage, interleave 64) against the oracle.  Eliminating the segments' interiors before their
-separators is Cholesky of a symmetric permutation of Omega, so the results are
+series of at least 96 steps, order 1 or 2, FP32 storage, interleave 64) against
+the oracle.  Eliminating the segments' interiors before their separators is Cholesky of a symmetric permutation of Omega, so the results are
 held to the bar of the sequential sweep: 1e-4 per series for FP32 storage (or
 the bound of the result's own backward error), componentwise backward error
 1e-6, adjoint 1e-4 and grad_lambda 10 times that.  The sizes cross the edges of
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [  # P, T, d, per_diff: 32 segments up to 2048 series
     (3, 512, 2, True), (5, 768, 1, False), (9, 769, 2, True), (17, 770, 2, False), (6, 745, 1, True),
-    (70, 1537, 2, True), (65, 1536 + 25, 1, True), (4, 3288, 2, True), (3, 3288, 1, False), (2, 6000, 2, False),
+    (11, 96, 2, True), (66, 97, 1, True), (9, 121, 2, False), (70, 1537, 2, True), (65, 1536 + 25, 1, True), (4, 3288, 2, True), (3, 3288, 1, False), (2, 6000, 2, False),
 ]
 
 
@@ -127,7 +127,7 @@ def _at_offset(t, k):
 
 
 @pytest.mark.parametrize("P,T,d,per_diff,k_x,k_w", [
-    (3, 512, 2, True, 0, 0), (70, 513, 2, True, 1, 1), (9, 1001, 1, False, 3, 2), (33, 770, 1, True, 0, 3),
+    (3, 512, 2, True, 0, 0), (1100, 101, 2, True, 1, 1), (70, 513, 2, True, 1, 1), (9, 1001, 1, False, 3, 2), (33, 770, 1, True, 0, 3),
     (130, 3288, 2, False, 2, 0), (2100, 600, 2, True, 1, 3), (4099, 531, 1, True, 0, 1), (8200, 517, 2, False, 1, 2),
     (16391, 523, 2, True, 3, 1),
 ])
