@@ -21,10 +21,14 @@
 // part from cancelling for series far from zero.
 //
 // G grid values share one pass: each tile of x and w is loaded once for G
-// recurrences, interleaved step by step.
+// recurrences, interleaved step by step.  A series' grid is spread over the
+// wavefronts of a block, and for small batches over lanes; every value's score
+// is the same in each form.
 #pragma once
 
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "whs_fast.h"
 
@@ -135,7 +139,7 @@ __device__ __forceinline__ void dual_step(DualState<D>& st, const double (&om)[D
   st.ed = v ? st.ed + e : st.ed;
 }
 
-template <int D, int B, typename TS, int G>
+template <int D, int B, typename TS, int G, int SL>
 struct Gcv : Fast<D, 1, B, TS, false, false> {
   using Base = Fast<D, 1, B, TS, false, false>;
   using typename Base::Tile;
@@ -192,13 +196,19 @@ struct Gcv : Fast<D, 1, B, TS, false, false> {
     }
   }
 
-  __device__ void run(const GcvArgs& g) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int wave_off = __builtin_amdgcn_readfirstlane((int)(threadIdx.x & ~63u));
-    const int64_t p0 = (int64_t)blockIdx.x * blockDim.x + wave_off;
-    if (p0 >= g.P) return;
-    const int64_t bidx = p0 / g.S;
-    const int s_in = (int)(p - bidx * g.S);
+  // Thread = (grid slot, series): a block holds 2^SL consecutive series of one
+  // block of the layout, and slot q of a series takes the groups of G grid
+  // values q, q + slots, ...  The slots' minima meet in shared memory at the end.
+  __device__ void run(const GcvArgs& g, double* sbest, int* sidx) {
+    constexpr int sl = SL;
+    const int slots = (int)blockDim.x >> sl;
+    const int tslot = (int)threadIdx.x >> sl;
+    const int slot = sl == 6 ? __builtin_amdgcn_readfirstlane(tslot) : tslot;
+    const int64_t p0 = (int64_t)blockIdx.x << sl;
+    const int lane = (int)threadIdx.x & ((1 << sl) - 1);
+    const int64_t p = p0 + lane;
+    const int64_t bidx = p0 / g.S;  // 2^SL divides S
+    const int s_in = (int)(p0 - bidx * g.S) + lane;
     this->T = g.T;
     this->S = g.S;
     this->Ctot = 1;
@@ -213,7 +223,7 @@ struct Gcv : Fast<D, 1, B, TS, false, false> {
     this->gb = nullptr;
     this->ckb = nullptr;
     this->accum = false;
-    const bool live = p < g.P;
+    const bool live = p < g.P;  // the lanes past the batch run to the barrier too
     constexpr uint32_t kDead = 0x80000000u;
     this->lx = live ? (uint32_t)s_in * (uint32_t)sizeof(TS) : kDead;
     this->lw = live ? (uint32_t)s_in : kDead;
@@ -223,8 +233,9 @@ struct Gcv : Fast<D, 1, B, TS, false, false> {
     double best = __builtin_huge_val();
     int best_i = -1;
     int first_info = 0;
-    for (int g0 = 0; g0 < g.n_grid; g0 += G) {
-      // a last group past the end of the grid repeats its last value (scores unused)
+    for (int gr = 0; gr < g.n_grid; gr += slots * G) {  // the same passes for every slot
+      const int g0 = gr + slot * G;
+      // values past the end of the grid repeat its last one (scores unused)
       double lam[G], omi[G][D + 1];
       DualState<D> st[G];
       int bad_tile[G];
@@ -241,28 +252,33 @@ struct Gcv : Fast<D, 1, B, TS, false, false> {
       int nobs = 0;
       Tile A, Bt;
       this->template load_tile<false>(A, 0);
-      for (int j = 0; j < nt; ++j) {
+      const auto tile = [&](auto inner, int j) {
         this->template load_tile<false>(Bt, (j + 1) * B);
         bool ok[G];
 #pragma unroll
         for (int c = 0; c < G; ++c) ok[c] = true;
-        if (interior(j * B)) tile_g<true>(st, A, j * B, lam, omi, ok, shift, have, sx, nobs);
-        else tile_g<false>(st, A, j * B, lam, omi, ok, shift, have, sx, nobs);
+        tile_g<decltype(inner)::value>(st, A, j * B, lam, omi, ok, shift, have, sx, nobs);
 #pragma unroll
         for (int c = 0; c < G; ++c)
           if (!ok[c] && bad_tile[c] < 0) bad_tile[c] = j;
         A = Bt;
-      }
+      };
+      // the edges of the series in loops of their own: the loop over interior
+      // tiles then keeps its whole state in registers
+      int j = 0;
+      for (; j < nt && !interior(j * B); ++j) tile(std::false_type{}, j);
+      for (; j < nt && interior(j * B); ++j) tile(std::true_type{}, j);
+      for (; j < nt; ++j) tile(std::false_type{}, j);
       const double m = (double)nobs;
 #pragma unroll
       for (int c = 0; c < G; ++c) {
+        const int gi = g0 + c;
         int info = 0;
-        if (live && bad_tile[c] >= 0) {
+        if (live && bad_tile[c] >= 0 && gi < g.n_grid) {
           this->lam_scalar = lam[c];
           info = this->first_bad_pivot((bad_tile[c] + 1) * B);
         }
         if (info == 0 && nobs < D) info = T;
-        const int gi = g0 + c;
         if (gi == 0) first_info = info;
         const double rss = sx - 2.0 * st[c].ds;
         const double den = m - st[c].ed;
@@ -276,17 +292,46 @@ struct Gcv : Fast<D, 1, B, TS, false, false> {
         }
       }
     }
-    if (live) {
+    sbest[threadIdx.x] = best;
+    sidx[threadIdx.x] = best_i;
+    __syncthreads();
+    if (slot == 0 && live) {
+      // a slot's minimum is its first; of equal minima the smallest index wins
+      for (int q = 1; q < slots; ++q) {
+        const double b = sbest[(q << sl) + lane];
+        const int i = sidx[(q << sl) + lane];
+        if (i >= 0 && (b < best || (b == best && i < best_i) || best_i < 0)) {
+          best = b;
+          best_i = i;
+        }
+      }
       static_cast<TS*>(g.lam_best)[p] = from_f64<TS>(best_i >= 0 ? g.grid[best_i] : __builtin_nan(""));
       if (g.info) g.info[p] = best_i >= 0 ? 0 : first_info;
     }
   }
 };
 
-template <int D, int B, typename TS, int G>
-__global__ __launch_bounds__(256) void k_gcv(GcvArgs a) {
-  Gcv<D, B, TS, G> k;
-  k.run(a);
+// NT: threads per block at most; W: wavefronts per SIMD that the registers must
+// allow.  Figures: 3288 days, 21 values, order 2, float64 (float32 within 6 %).
+//
+// Bound by the issue of float64 instructions: 31 and a reciprocal per row and
+// value, and eleven others per row for the inputs, against 9 bytes per row and
+// pass.  One wavefront per 64 series leaves most of the chip idle below 65,536
+// series (5.6 ms for 64 series, 6.3 ms for 65,536), so the grid is spread over
+// the wavefronts of a block, and below 8,192 series over lanes as well:
+//   series      64    4,096   8,192   16,384   32,768   49,152   65,536
+//   SL 3, G 1  0.43   0.77    1.17     2.21     4.15     5.98     8.07 ms
+//   SL 6, G 3  1.47   1.51    1.51     1.59     3.12     4.66     6.19 ms
+//   SL 6, G 7  5.18   5.20    5.20     5.21     5.27     5.26     5.72 ms
+// (the last in one wavefront).  The wavefronts of a block read the same rows
+// within a short time of each other, out of the caches.  Tiles of 4 rows: with
+// eight the two tiles in flight take 24 registers more.
+template <int D, int B, typename TS, int G, int SL, int NT, int W>
+__global__ __launch_bounds__(NT, W) void k_gcv(GcvArgs a) {
+  __shared__ double sbest[NT];
+  __shared__ int sidx[NT];
+  Gcv<D, B, TS, G, SL> k;
+  k.run(a, sbest, sidx);
 }
 
 }  // namespace whs
