@@ -460,8 +460,8 @@ __global__ __launch_bounds__(256) void k_wgrad(const void* __restrict__ dy, int 
 // lane 8 keys, {4g..4g+3} and {16+4g..16+4g+3} with g = lane/16, which is
 // exactly the K slice a lane supplies as the B operand of the next MFMA: the
 // probabilities (or score gradients) go from accumulator to operand without
-// leaving the lane, and the other operand reads the same keys from a
-// transposed copy in LDS.  Probabilities and score gradients are split into a
+// leaving the lane, and the other operand reads the same keys transposed from LDS
+// (by transposing reads; the forward from a transposed copy).  Probabilities and score gradients are split into a
 // bfloat16 high part and a bfloat16 remainder (two MFMAs), which keeps about 16
 // significant bits; scores and value products are exact bfloat16 products
 // summed in FP32.
@@ -470,27 +470,59 @@ constexpr float kScale = 0.17677669529663688f;  // 1/sqrt(32)
 constexpr float kScale2 = 0.25503486280989163f;  // kScale log2(e): scores in powers of two
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr int ATN = 32;         // queries (keys) per wavefront: two columns of 16
-constexpr int RSD = DH + 8;     // row-major LDS stride (bf16): 80 bytes
 
 __device__ __forceinline__ u32x4 ld16(const uint16_t* p) { return *reinterpret_cast<const u32x4*>(p); }
 
+// One head's 32 columns of staged rows lie in LDS as rows of 64 bytes whose
+// 16-byte chunks are permuted by XOR with swz(row): a row-major fragment (16 rows,
+// one chunk each) and a transposing read (8 rows, two chunks each) both touch all
+// 64 banks once.
+__device__ __forceinline__ int swz(int row) { return (row >> 1 & 2) | (row >> 3 & 1); }
+
+// rows r0 .. r0+nr-1 of one head's 32 columns, and zero rows up to a multiple of
+// 32; a thread's rows lie whole wavefronts of 16 rows apart and share their swz()
+__device__ __forceinline__ void stage_r(uint16_t* dst, const uint16_t* base, int64_t stride, int col, int r0, int nr) {
+  const int c = threadIdx.x & 3, n32 = (nr + 31) & ~31;
+  int r = threadIdx.x >> 2;
+  const uint16_t* src = base + (int64_t)(r0 + r) * stride + col + 8 * c;
+  uint16_t* to = dst + r * DH + 8 * (c ^ swz(r));
+#pragma unroll 2
+  for (const int step = blockDim.x >> 2; r < n32; r += step, src += step * stride, to += step * DH) {
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (r < nr) v = ld16(src);
+    *reinterpret_cast<u32x4*>(to) = v;
+  }
+}
+// row-major operand of 16 rows from b (a multiple of 16): row b + c, columns 8g .. 8g+7
+__device__ __forceinline__ bf16x8 ld_r(const uint16_t* r, int b, int g, int c) {
+  return __builtin_bit_cast(bf16x8, ld16(r + (b + c) * DH + 8 * (g ^ swz(c))));
+}
+// transposed operand: column ch + c (ch 0 or 16), the 8 rows {b+4g..b+4g+3,
+// b+16+4g..+3}.  A transposing read hands lane c of 16 lanes the column c of the
+// four 32-byte row pieces that those lanes point at, four lanes to a row.
+__device__ __forceinline__ bf16x8 ld_t(const uint16_t* t, int ch, int b, int g, int c) {
+  typedef __attribute__((ext_vector_type(4))) short s16x4;
+  typedef __attribute__((address_space(3))) s16x4* lp;
+  const int row = 4 * g + (c >> 2), chunk = ch / 8 + (c >> 1 & 1);
+  uint16_t* src = const_cast<uint16_t*>(t) + (b + row) * DH + 8 * (chunk ^ swz(row)) + 4 * (c & 1);
+  const s16x4 x = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)src);
+  const s16x4 y = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(src + 16 * DH));
+  const u32x2 xu = __builtin_bit_cast(u32x2, x), yu = __builtin_bit_cast(u32x2, y);
+  return __builtin_bit_cast(bf16x8, u32x4{xu[0], xu[1], yu[0], yu[1]});
+}
+
+// The forward kernel keeps a padded row-major copy of the keys and a transposed
+// copy of the values instead: with transposing reads it takes 91 registers for 78,
+// one workgroup of twelve wavefronts on a CU for two (4096 series of 280 rows:
+// 0.39 ms for 0.34).
+constexpr int RSD = DH + 8;     // row-major LDS stride (bf16): 80 bytes
 // stride (bf16) of a transposed copy of ch rows: 20 dwords past a multiple of the
 // 64 banks, where the 16 channel rows of a read spread over all of them (at 4
-// past, the backward of 4096 series of 128 rows took 295 us for 245)
+// past, an earlier backward of 4096 series of 128 rows took 295 us for 245)
 constexpr int tsd(int ch) {
   int t = ch + 8;
   while (t / 2 % 64 != 20) t += 2;
   return t;
-}
-// rows r0 .. r0+CH-1 (zero from nr on) of one head's 32 columns, row-major, stride RSD
-template <int CH>
-__device__ __forceinline__ void stage_r(uint16_t* dst, const uint16_t* base, int64_t stride, int col, int r0, int nr) {
-  for (int i = threadIdx.x; i < CH * 4; i += blockDim.x) {
-    const int r = i >> 2, c = i & 3;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (r < nr) v = ld16(base + (int64_t)(r0 + r) * stride + col + 8 * c);
-    *reinterpret_cast<u32x4*>(dst + r * RSD + 8 * c) = v;
-  }
 }
 // the same rows transposed, dst[channel][row], stride tsd(CH); pairs of rows per 4-byte store
 template <int CH>
@@ -507,29 +539,40 @@ __device__ __forceinline__ void stage_t(uint16_t* dst, const uint16_t* base, int
     }
   }
 }
-// transposed copy of an LDS row-major copy (rows past the end are already zero)
+// rows r0 .. r0+CH-1 (zero from nr on) of one head's 32 columns, row-major, stride RSD
 template <int CH>
-__device__ __forceinline__ void transpose_lds(uint16_t* dst, const uint16_t* src) {
-  for (int i = threadIdx.x; i < (CH / 2) * 4; i += blockDim.x) {
-    const int j = i >> 2, c = i & 3;
-    const u32x4 v0 = *reinterpret_cast<const u32x4*>(src + (2 * j) * RSD + 8 * c);
-    const u32x4 v1 = *reinterpret_cast<const u32x4*>(src + (2 * j + 1) * RSD + 8 * c);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      *reinterpret_cast<uint32_t*>(dst + (8 * c + 2 * q) * tsd(CH) + 2 * j) = (v0[q] & 0xffffu) | (v1[q] << 16);
-      *reinterpret_cast<uint32_t*>(dst + (8 * c + 2 * q + 1) * tsd(CH) + 2 * j) = (v0[q] >> 16) | (v1[q] & 0xffff0000u);
-    }
+__device__ __forceinline__ void stage_p(uint16_t* dst, const uint16_t* base, int64_t stride, int col, int r0, int nr) {
+  for (int i = threadIdx.x; i < CH * 4; i += blockDim.x) {
+    const int r = i >> 2, c = i & 3;
+    u32x4 v = {0u, 0u, 0u, 0u};
+    if (r < nr) v = ld16(base + (int64_t)(r0 + r) * stride + col + 8 * c);
+    *reinterpret_cast<u32x4*>(dst + r * RSD + 8 * c) = v;
   }
+}
+__device__ __forceinline__ bf16x8 ld_p(const uint16_t* r, int row, int g) {
+  return __builtin_bit_cast(bf16x8, ld16(r + row * RSD + 8 * g));
 }
 // A operand from a transposed copy: channel row ch, the 8 rows {b+4g..b+4g+3, b+16+4g..+3}
 template <int CH>
-__device__ __forceinline__ bf16x8 ld_t(const uint16_t* t, int ch, int b, int g) {
+__device__ __forceinline__ bf16x8 ld_c(const uint16_t* t, int ch, int b, int g) {
   const u32x2 x = *reinterpret_cast<const u32x2*>(t + ch * tsd(CH) + b + 4 * g);
   const u32x2 y = *reinterpret_cast<const u32x2*>(t + ch * tsd(CH) + b + 16 + 4 * g);
   return __builtin_bit_cast(bf16x8, u32x4{x[0], x[1], y[0], y[1]});
 }
-__device__ __forceinline__ bf16x8 ld_r(const uint16_t* r, int row, int g) {
-  return __builtin_bit_cast(bf16x8, ld16(r + row * RSD + 8 * g));
+// v minus the low (high) bfloat16 of the pair h in one instruction, a dot product
+// with (-1, 0) and (0, -1) added to v: exact.  The factors go through scalar
+// registers, since an inline constant of this instruction stands for both halves.
+__device__ __forceinline__ float sub_lo(float v, uint32_t h) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  uint32_t k = 0x0000bf80u;
+  asm("" : "+s"(k));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf2, h), __builtin_bit_cast(bf2, k), v, false);
+}
+__device__ __forceinline__ float sub_hi(float v, uint32_t h) {
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  uint32_t k = 0xbf800000u;
+  asm("" : "+s"(k));
+  return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf2, h), __builtin_bit_cast(bf2, k), v, false);
 }
 // 8 FP32 values -> bfloat16 high parts and bfloat16 remainders
 __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& lo) {
@@ -537,7 +580,7 @@ __device__ __forceinline__ void split8(const float* v, bf16x8& hi, bf16x8& lo) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     h[q] = pack2(v[2 * q], v[2 * q + 1]);
-    l[q] = pack2(v[2 * q] - lo_bf(h[q]), v[2 * q + 1] - hi_bf(h[q]));
+    l[q] = pack2(sub_lo(v[2 * q], h[q]), sub_hi(v[2 * q + 1], h[q]));
   }
   hi = __builtin_bit_cast(bf16x8, h);
   lo = __builtin_bit_cast(bf16x8, l);
@@ -561,25 +604,36 @@ __device__ __forceinline__ void st4(uint16_t* dst, f32x4 v, float s) {
 // What bounds these kernels is the vector work on the T x T probabilities (the
 // exponential, its split and their masks), not the matrix products or the
 // bytes.  So a wavefront takes two columns of 16 queries (keys): each LDS read
-// of the other side feeds both.  The workgroups of a (series, head) share its
-// rows evenly (280 rows: two workgroups of 5 wavefronts, 9 of 10 busy).  Scores go to
-// powers of two in one FMA, only the last block of a chunk is masked, and the
-// forward takes the maximum of a chunk in a first pass over its scores, so that
-// nothing is rescaled inside the second.
+// of the other side feeds both.  Scores go to powers of two in one FMA, only the
+// last block of a chunk is masked, a remainder of the split is one instruction, and
+// the forward takes the maximum of a chunk in a first pass over its scores, so that
+// nothing is rescaled inside the second.  The launch bounds name the wavefronts per
+// SIMD that LDS leaves room for: with fewer the compiler moved the sums to the
+// accumulation registers and back in every block (the backward of 4096 series of
+// 280 rows: 0.84 ms for 0.80).
 
-// Which (series, head) and which part of its rows a workgroup takes.  A token's
-// 64 bytes of one head are half a cache line, so the heads and parts of a series
-// run one after the other on one XCD (dispatch is round-robin over 8): each L2
-// then fetches a line once and joins the halves written to it.
+// Which (series, head) a workgroup takes, and from which block of ATN rows on.  A
+// token's 64 bytes of one head are half a cache line, so the heads and parts of a
+// series run one after the other on one XCD (dispatch is round-robin over 8): each
+// L2 then fetches a line once and joins the halves written to it.
 struct AttnWg {
   int64_t p;
-  int hd, part;
+  int hd, blk;
 };
-__device__ __forceinline__ AttnWg attn_wg(int T) {
+__device__ __forceinline__ AttnWg attn_wg(int T, int rounds) {
   const unsigned n = gridDim.x, q = n / 8, r = n % 8, xcd = blockIdx.x % 8;
   const unsigned id = xcd * q + (xcd < r ? xcd : r) + blockIdx.x / 8;
-  const unsigned rows = (blockDim.x >> 6) * ATN, parts = ((unsigned)T + rows - 1) / rows;
-  return AttnWg{(int64_t)(id / (NH * parts)), (int)(id / parts % NH), (int)(id % parts)};
+  const unsigned per = (blockDim.x >> 6) * (unsigned)rounds, rows = per * ATN, parts = ((unsigned)T + rows - 1) / rows;
+  return AttnWg{(int64_t)(id / (NH * parts)), (int)(id / parts % NH), (int)(id % parts * per)};
+}
+
+// The wavefront's place among a workgroup's W.  A workgroup of four that takes 9
+// blocks in three rounds leaves three places empty in the last one; turning the
+// places with the workgroup spreads the full ones over the SIMDs of a CU.
+template <int W>
+__device__ __forceinline__ int attn_wave() {
+  const unsigned w = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  return (int)((w + blockIdx.x / 8 + blockIdx.x / 256) % W);
 }
 
 // exp2(s k - m) of 8 scores, zero from row nv on
@@ -607,7 +661,7 @@ template <bool MASK>
 __device__ __forceinline__ void max_block(const uint16_t* ks, int kb, int nv, int g, int c, const FwdCol (&col)[2],
                                           float (&bm)[2]) {
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-  const bf16x8 k0 = ld_r(ks, kb + c, g), k1 = ld_r(ks, kb + 16 + c, g);
+  const bf16x8 k0 = ld_p(ks, kb + c, g), k1 = ld_p(ks, kb + 16 + c, g);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     f32x4 sa = mfma(k0, col[u].q, z4), sb = mfma(k1, col[u].q, z4);
@@ -627,8 +681,8 @@ template <bool MASK, int CH>
 __device__ __forceinline__ void fwd_block(const uint16_t* ks, const uint16_t* vt, int kb, int nv, int g, int c,
                                           FwdCol (&col)[2]) {
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-  const bf16x8 k0 = ld_r(ks, kb + c, g), k1 = ld_r(ks, kb + 16 + c, g);
-  const bf16x8 v0 = ld_t<CH>(vt, c, kb, g), v1 = ld_t<CH>(vt, 16 + c, kb, g);
+  const bf16x8 k0 = ld_p(ks, kb + c, g), k1 = ld_p(ks, kb + 16 + c, g);
+  const bf16x8 v0 = ld_c<CH>(vt, c, kb, g), v1 = ld_c<CH>(vt, 16 + c, kb, g);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     float e[8];
@@ -652,13 +706,13 @@ __global__ __launch_bounds__(64 * W) void k_attn_fwd(const uint16_t* __restrict_
                                                        uint16_t* __restrict__ o, float* __restrict__ lse) {
   __shared__ __attribute__((aligned(16))) uint16_t ks[CH * RSD];
   __shared__ __attribute__((aligned(16))) uint16_t vt[DH * tsd(CH)];
-  const AttnWg wg = attn_wg(T);
+  const AttnWg wg = attn_wg(T, 1);
   const int64_t p = wg.p;
   const int hd = wg.hd;
   const uint16_t* base = qkv + p * (int64_t)T * QKV;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int g = lane >> 4, c = lane & 15;
-  const int q0 = (wg.part * (int)(blockDim.x >> 6) + wave) * ATN;
+  const int q0 = (wg.blk + wave) * ATN;
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
   FwdCol col[2];
 #pragma unroll
@@ -671,7 +725,7 @@ __global__ __launch_bounds__(64 * W) void k_attn_fwd(const uint16_t* __restrict_
   for (int c0 = 0; c0 < T; c0 += CH) {
     const int nk = T - c0 < CH ? T - c0 : CH;
     __syncthreads();
-    stage_r<CH>(ks, base, QKV, E + DH * hd, c0, nk);
+    stage_p<CH>(ks, base, QKV, E + DH * hd, c0, nk);
     stage_t<CH>(vt, base, QKV, 2 * E + DH * hd, c0, nk);
     __syncthreads();
     if (q0 >= T) continue;
@@ -709,13 +763,13 @@ struct BwdQCol {
   f32x4 acc[2];
 };
 
-template <bool MASK, int CH>
-__device__ __forceinline__ void bwd_q_block(const uint16_t* ks, const uint16_t* vs, const uint16_t* kt, int kb, int nv,
-                                            int g, int c, BwdQCol (&col)[2]) {
+template <bool MASK>
+__device__ __forceinline__ void bwd_q_block(const uint16_t* ks, const uint16_t* vs, int kb, int nv, int g, int c,
+                                            BwdQCol (&col)[2]) {
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-  const bf16x8 k0 = ld_r(ks, kb + c, g), k1 = ld_r(ks, kb + 16 + c, g);
-  const bf16x8 v0 = ld_r(vs, kb + c, g), v1 = ld_r(vs, kb + 16 + c, g);
-  const bf16x8 t0 = ld_t<CH>(kt, c, kb, g), t1 = ld_t<CH>(kt, 16 + c, kb, g);
+  const bf16x8 k0 = ld_r(ks, kb, g, c), k1 = ld_r(ks, kb + 16, g, c);
+  const bf16x8 v0 = ld_r(vs, kb, g, c), v1 = ld_r(vs, kb + 16, g, c);
+  const bf16x8 t0 = ld_t(ks, 0, kb, g, c), t1 = ld_t(ks, 16, kb, g, c);
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     float ds[8];
@@ -734,196 +788,212 @@ __device__ __forceinline__ void bwd_q_block(const uint16_t* ks, const uint16_t* 
 }
 
 // Query gradient: dq = scale sum_k p (dp - delta) k.  Lane (g, c) owns queries c
-// and 16 + c of its wave; keys, values (row-major) and keys (transposed) staged
-// per chunk.
+// and 16 + c of its wave; keys and values staged per chunk.
 template <int W, int CH>
-__global__ __launch_bounds__(64 * W) void k_attn_bwd_q(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ o,
-                                                         const uint16_t* __restrict__ go, const float* __restrict__ lse,
-                                                         int T, uint16_t* __restrict__ dqkv) {
-  __shared__ __attribute__((aligned(16))) uint16_t ks[CH * RSD];
-  __shared__ __attribute__((aligned(16))) uint16_t vs[CH * RSD];
-  __shared__ __attribute__((aligned(16))) uint16_t kt[DH * tsd(CH)];
-  const AttnWg wg = attn_wg(T);
+__global__ __launch_bounds__(64 * W, CH == 384 ? 3 : 4) void k_attn_bwd_q(
+    const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ o, const uint16_t* __restrict__ go,
+    const float* __restrict__ lse, int T, int rounds, uint16_t* __restrict__ dqkv) {
+  __shared__ __attribute__((aligned(16))) uint16_t ks[CH * DH];
+  __shared__ __attribute__((aligned(16))) uint16_t vs[CH * DH];
+  const AttnWg wg = attn_wg(T, rounds);
   const int64_t p = wg.p;
   const int hd = wg.hd;
   const uint16_t* base = qkv + p * (int64_t)T * QKV;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, wave = attn_wave<W>();
   const int g = lane >> 4, c = lane & 15;
-  const int q0 = (wg.part * (int)(blockDim.x >> 6) + wave) * ATN;
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-  BwdQCol col[2];
+  for (int r = 0; r < rounds; ++r) {
+    const int q0 = (wg.blk + r * W + wave) * ATN;
+    BwdQCol col[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int qi = q0 + 16 * u + c;
-    u32x4 qv = {0u, 0u, 0u, 0u}, dv = {0u, 0u, 0u, 0u}, ov = {0u, 0u, 0u, 0u};
-    float L = 0.f;
-    if (qi < T) {
-      qv = ld16(base + (int64_t)qi * QKV + DH * hd + 8 * g);
-      dv = ld16(go + (p * T + qi) * (int64_t)E + DH * hd + 8 * g);
-      ov = ld16(o + (p * T + qi) * (int64_t)E + DH * hd + 8 * g);
-      L = lse[(p * NH + hd) * (int64_t)T + qi] * kLog2e;
+    for (int u = 0; u < 2; ++u) {
+      const int qi = q0 + 16 * u + c;
+      u32x4 qv = {0u, 0u, 0u, 0u}, dv = {0u, 0u, 0u, 0u}, ov = {0u, 0u, 0u, 0u};
+      float L = 0.f;
+      if (qi < T) {
+        qv = ld16(base + (int64_t)qi * QKV + DH * hd + 8 * g);
+        dv = ld16(go + (p * T + qi) * (int64_t)E + DH * hd + 8 * g);
+        ov = ld16(o + (p * T + qi) * (int64_t)E + DH * hd + 8 * g);
+        L = lse[(p * NH + hd) * (int64_t)T + qi] * kLog2e;
+      }
+      float dl = 0.f;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) dl += lo_bf(dv[q]) * lo_bf(ov[q]) + hi_bf(dv[q]) * hi_bf(ov[q]);
+      col[u] = BwdQCol{__builtin_bit_cast(bf16x8, qv), __builtin_bit_cast(bf16x8, dv), L, sum_g(dl), {z4, z4}};
     }
-    float dl = 0.f;
+    for (int c0 = 0; c0 < T; c0 += CH) {
+      const int nk = T - c0 < CH ? T - c0 : CH;
+      if (r == 0 || T > CH) {
+        __syncthreads();
+        stage_r(ks, base, QKV, E + DH * hd, c0, nk);
+        stage_r(vs, base, QKV, 2 * E + DH * hd, c0, nk);
+        __syncthreads();
+      }
+      if (q0 >= T) continue;
+      int kb = 0;
+#pragma unroll 1
+      for (; kb + 32 <= nk; kb += 32) bwd_q_block<false>(ks, vs, kb, 32, g, c, col);
+      if (kb < nk) bwd_q_block<true>(ks, vs, kb, nk - kb, g, c, col);
+    }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) dl += lo_bf(dv[q]) * lo_bf(ov[q]) + hi_bf(dv[q]) * hi_bf(ov[q]);
-    col[u] = BwdQCol{__builtin_bit_cast(bf16x8, qv), __builtin_bit_cast(bf16x8, dv), L, sum_g(dl), {z4, z4}};
-  }
-  for (int c0 = 0; c0 < T; c0 += CH) {
-    const int nk = T - c0 < CH ? T - c0 : CH;
-    __syncthreads();
-    stage_r<CH>(ks, base, QKV, E + DH * hd, c0, nk);
-    stage_r<CH>(vs, base, QKV, 2 * E + DH * hd, c0, nk);
-    __syncthreads();
-    transpose_lds<CH>(kt, ks);
-    __syncthreads();
-    if (q0 >= T) continue;
-    int kb = 0;
-    for (; kb + 32 <= nk; kb += 32) bwd_q_block<false, CH>(ks, vs, kt, kb, 32, g, c, col);
-    if (kb < nk) bwd_q_block<true, CH>(ks, vs, kt, kb, nk - kb, g, c, col);
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int qi = q0 + 16 * u + c;
-    if (qi >= T) continue;
-    uint16_t* dst = dqkv + (p * T + qi) * (int64_t)QKV + DH * hd;
-    st4(dst + 4 * g, col[u].acc[0], kScale);
-    st4(dst + 16 + 4 * g, col[u].acc[1], kScale);
+    for (int u = 0; u < 2; ++u) {
+      const int qi = q0 + 16 * u + c;
+      if (qi >= T) continue;
+      uint16_t* dst = dqkv + (p * T + qi) * (int64_t)QKV + DH * hd;
+      st4(dst + 4 * g, col[u].acc[0], kScale);
+      st4(dst + 16 + 4 * g, col[u].acc[1], kScale);
+    }
   }
 }
 
 // Key and value gradients: dv = sum_q p do, dk = scale sum_q p (dp - delta) q.
-// Lane (g, c) owns keys c and 16 + c of its wave; queries (row-major and
-// transposed), output gradients (both), log-sum-exps and deltas staged per
-// chunk; rows past the end carry an infinite log-sum-exp, so p is 0 there.
+// Lane (g, c) owns keys c and 16 + c of its wave; queries, output gradients,
+// log-sum-exps and deltas staged per chunk; rows past the end carry an infinite
+// log-sum-exp, so p is 0 there.
 template <int W, int CH>
-__global__ __launch_bounds__(64 * W, W == 8 ? 4 : 3) void k_attn_bwd_kv(const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ o,
-                                                          const uint16_t* __restrict__ go, const float* __restrict__ lse,
-                                                          int T, uint16_t* __restrict__ dqkv) {
-  __shared__ __attribute__((aligned(16))) uint16_t qs[CH * RSD];
-  __shared__ __attribute__((aligned(16))) uint16_t dos[CH * RSD];
-  __shared__ __attribute__((aligned(16))) uint16_t qt[DH * tsd(CH)];
-  __shared__ __attribute__((aligned(16))) uint16_t dt[DH * tsd(CH)];
+__global__ __launch_bounds__(64 * W, W == 8 ? 4 : 3) void k_attn_bwd_kv(
+    const uint16_t* __restrict__ qkv, const uint16_t* __restrict__ o, const uint16_t* __restrict__ go,
+    const float* __restrict__ lse, int T, int rounds, uint16_t* __restrict__ dqkv) {
+  __shared__ __attribute__((aligned(16))) uint16_t qs[CH * DH];
+  __shared__ __attribute__((aligned(16))) uint16_t dos[CH * DH];
   __shared__ __attribute__((aligned(16))) float ls[CH];
   __shared__ __attribute__((aligned(16))) float dl[CH];
-  const AttnWg wg = attn_wg(T);
+  const AttnWg wg = attn_wg(T, rounds);
   const int64_t p = wg.p;
   const int hd = wg.hd;
   const uint16_t* base = qkv + p * (int64_t)T * QKV;
   const uint16_t* gob = go + p * (int64_t)T * E;
   const uint16_t* ob = o + p * (int64_t)T * E;
   const float* lb = lse + (p * NH + hd) * (int64_t)T;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int lane = threadIdx.x & 63, wave = attn_wave<W>();
   const int g = lane >> 4, c = lane & 15;
-  const int j0 = (wg.part * (int)(blockDim.x >> 6) + wave) * ATN;
   const f32x4 z4 = {0.f, 0.f, 0.f, 0.f};
-  bf16x8 kb8[2], vb8[2];
-  f32x4 adv[2][2], adk[2][2];
+  for (int r = 0; r < rounds; ++r) {
+    const int j0 = (wg.blk + r * W + wave) * ATN;
+    bf16x8 kb8[2], vb8[2];
+    f32x4 adv[2][2], adk[2][2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int kj = j0 + 16 * u + c;
-    u32x4 kv = {0u, 0u, 0u, 0u}, vv = {0u, 0u, 0u, 0u};
-    if (kj < T) {
-      kv = ld16(base + (int64_t)kj * QKV + E + DH * hd + 8 * g);
-      vv = ld16(base + (int64_t)kj * QKV + 2 * E + DH * hd + 8 * g);
-    }
-    kb8[u] = __builtin_bit_cast(bf16x8, kv);
-    vb8[u] = __builtin_bit_cast(bf16x8, vv);
-    adv[u][0] = adv[u][1] = adk[u][0] = adk[u][1] = z4;
-  }
-  for (int c0 = 0; c0 < T; c0 += CH) {
-    const int nq = T - c0 < CH ? T - c0 : CH;
-    __syncthreads();
-    stage_r<CH>(qs, base, QKV, DH * hd, c0, nq);
-    stage_r<CH>(dos, gob, E, DH * hd, c0, nq);
-    __syncthreads();
-    transpose_lds<CH>(qt, qs);
-    transpose_lds<CH>(dt, dos);
-    for (int r = threadIdx.x; r < CH; r += blockDim.x) {
-      float d = 0.f, L = INFINITY;
-      if (r < nq) {
-        const uint16_t* b = ob + (int64_t)(c0 + r) * E + DH * hd;
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-          const u32x4 x = *reinterpret_cast<const u32x4*>(dos + r * RSD + 8 * cc), y = ld16(b + 8 * cc);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) d += lo_bf(x[q]) * lo_bf(y[q]) + hi_bf(x[q]) * hi_bf(y[q]);
-        }
-        L = lb[c0 + r] * kLog2e;
+    for (int u = 0; u < 2; ++u) {
+      const int kj = j0 + 16 * u + c;
+      u32x4 kv = {0u, 0u, 0u, 0u}, vv = {0u, 0u, 0u, 0u};
+      if (kj < T) {
+        kv = ld16(base + (int64_t)kj * QKV + E + DH * hd + 8 * g);
+        vv = ld16(base + (int64_t)kj * QKV + 2 * E + DH * hd + 8 * g);
       }
-      dl[r] = d;
-      ls[r] = L;
+      kb8[u] = __builtin_bit_cast(bf16x8, kv);
+      vb8[u] = __builtin_bit_cast(bf16x8, vv);
+      adv[u][0] = adv[u][1] = adk[u][0] = adk[u][1] = z4;
     }
-    __syncthreads();
-    if (j0 >= T) continue;
-    for (int qb = 0; qb < nq; qb += 32) {
-      // scores and output-gradient products, queries as rows: lane holds queries 4g+r of each half
-      const bf16x8 q0 = ld_r(qs, qb + c, g), q1 = ld_r(qs, qb + 16 + c, g);
-      const bf16x8 d0 = ld_r(dos, qb + c, g), d1 = ld_r(dos, qb + 16 + c, g);
-      const bf16x8 dt0 = ld_t<CH>(dt, c, qb, g), dt1 = ld_t<CH>(dt, 16 + c, qb, g);
-      const bf16x8 qt0 = ld_t<CH>(qt, c, qb, g), qt1 = ld_t<CH>(qt, 16 + c, qb, g);
-      // statistics of queries qb+4g..+3 and qb+16+4g..+3: four 16-byte reads
-      const f32x4 la = *reinterpret_cast<const f32x4*>(ls + qb + 4 * g);
-      const f32x4 lb4 = *reinterpret_cast<const f32x4*>(ls + qb + 16 + 4 * g);
-      const f32x4 da = *reinterpret_cast<const f32x4*>(dl + qb + 4 * g);
-      const f32x4 db = *reinterpret_cast<const f32x4*>(dl + qb + 16 + 4 * g);
+    for (int c0 = 0; c0 < T; c0 += CH) {
+      const int nq = T - c0 < CH ? T - c0 : CH;
+      if (r == 0 || T > CH) {
+        __syncthreads();
+        stage_r(qs, base, QKV, DH * hd, c0, nq);
+        stage_r(dos, gob, E, DH * hd, c0, nq);
+        __syncthreads();
+        for (int i = threadIdx.x; i < ((nq + 31) & ~31); i += 64 * W) {
+          float d = 0.f, L = INFINITY;
+          if (i < nq) {
+            const uint16_t* b = ob + (int64_t)(c0 + i) * E + DH * hd;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const f32x4 sa = mfma(q0, kb8[u], z4), sb = mfma(q1, kb8[u], z4);
-        const f32x4 pa = mfma(d0, vb8[u], z4), pb = mfma(d1, vb8[u], z4);
-        float pr[8], ds[8];
+            for (int cc = 0; cc < 4; ++cc) {
+              const u32x4 x = *reinterpret_cast<const u32x4*>(dos + i * DH + 8 * (cc ^ swz(i))), y = ld16(b + 8 * cc);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          pr[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[r], kScale2, -la[r]));
-          pr[4 + r] = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[r], kScale2, -lb4[r]));
-          ds[r] = pr[r] * (pa[r] - da[r]);
-          ds[4 + r] = pr[4 + r] * (pb[r] - db[r]);
+              for (int q = 0; q < 4; ++q) d += lo_bf(x[q]) * lo_bf(y[q]) + hi_bf(x[q]) * hi_bf(y[q]);
+            }
+            L = lb[c0 + i] * kLog2e;
+          }
+          dl[i] = d;
+          ls[i] = L;
         }
-        bf16x8 ph, pl, hh, ll;
-        split8(pr, ph, pl);
-        split8(ds, hh, ll);
-        adv[u][0] = mfma(dt0, ph, mfma(dt0, pl, adv[u][0]));
-        adv[u][1] = mfma(dt1, ph, mfma(dt1, pl, adv[u][1]));
-        adk[u][0] = mfma(qt0, hh, mfma(qt0, ll, adk[u][0]));
-        adk[u][1] = mfma(qt1, hh, mfma(qt1, ll, adk[u][1]));
+        __syncthreads();
+      }
+      if (j0 >= T) continue;
+#pragma unroll 1
+      for (int qb = 0; qb < nq; qb += 32) {
+        // scores and output-gradient products, queries as rows: lane holds queries 4g+r of each half
+        const bf16x8 q0 = ld_r(qs, qb, g, c), q1 = ld_r(qs, qb + 16, g, c);
+        const bf16x8 d0 = ld_r(dos, qb, g, c), d1 = ld_r(dos, qb + 16, g, c);
+        const bf16x8 dt0 = ld_t(dos, 0, qb, g, c), dt1 = ld_t(dos, 16, qb, g, c);
+        const bf16x8 qt0 = ld_t(qs, 0, qb, g, c), qt1 = ld_t(qs, 16, qb, g, c);
+        // statistics of queries qb+4g..+3 and qb+16+4g..+3: four 16-byte reads
+        const f32x4 la = *reinterpret_cast<const f32x4*>(ls + qb + 4 * g);
+        const f32x4 lb4 = *reinterpret_cast<const f32x4*>(ls + qb + 16 + 4 * g);
+        const f32x4 da = *reinterpret_cast<const f32x4*>(dl + qb + 4 * g);
+        const f32x4 db = *reinterpret_cast<const f32x4*>(dl + qb + 16 + 4 * g);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const f32x4 sa = mfma(q0, kb8[u], z4), sb = mfma(q1, kb8[u], z4);
+          const f32x4 pa = mfma(d0, vb8[u], z4), pb = mfma(d1, vb8[u], z4);
+          float pr[8], ds[8];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            pr[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e], kScale2, -la[e]));
+            pr[4 + e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sb[e], kScale2, -lb4[e]));
+            ds[e] = pr[e] * (pa[e] - da[e]);
+            ds[4 + e] = pr[4 + e] * (pb[e] - db[e]);
+          }
+          bf16x8 ph, pl, hh, ll;
+          split8(pr, ph, pl);
+          split8(ds, hh, ll);
+          adv[u][0] = mfma(dt0, ph, mfma(dt0, pl, adv[u][0]));
+          adv[u][1] = mfma(dt1, ph, mfma(dt1, pl, adv[u][1]));
+          adk[u][0] = mfma(qt0, hh, mfma(qt0, ll, adk[u][0]));
+          adk[u][1] = mfma(qt1, hh, mfma(qt1, ll, adk[u][1]));
+        }
       }
     }
-  }
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int kj = j0 + 16 * u + c;
-    if (kj >= T) continue;
-    uint16_t* dst = dqkv + (p * T + kj) * (int64_t)QKV + DH * hd;
-    st4(dst + E + 4 * g, adk[u][0], kScale);
-    st4(dst + E + 16 + 4 * g, adk[u][1], kScale);
-    st4(dst + 2 * E + 4 * g, adv[u][0], 1.f);
-    st4(dst + 2 * E + 16 + 4 * g, adv[u][1], 1.f);
+    for (int u = 0; u < 2; ++u) {
+      const int kj = j0 + 16 * u + c;
+      if (kj >= T) continue;
+      uint16_t* dst = dqkv + (p * T + kj) * (int64_t)QKV + DH * hd;
+      st4(dst + E + 4 * g, adk[u][0], kScale);
+      st4(dst + E + 16 + 4 * g, adk[u][1], kScale);
+      st4(dst + 2 * E + 4 * g, adv[u][0], 1.f);
+      st4(dst + 2 * E + 16 + 4 * g, adv[u][1], 1.f);
+    }
   }
 }
 
-// Wavefronts per workgroup and rows staged at a time.  Workgroups are whole
-// multiples of four wavefronts, so that the SIMDs share the work (4096 series of
-// 280 rows, forward and backward: 1.84 ms with two workgroups of 5, 1.47 with one
-// of 12, 2.13 with 8 wavefronts of 16 rows).  Up to 384 rows one
-// workgroup holds a whole (series, head) and up to 288 rows arrive at once: the
-// wait for them comes once (160 rows at a time: 1.58 ms).  Longer series take 8
+// Forward: whole multiples of four wavefronts, so that the SIMDs share the work.
+// Up to 384 rows one workgroup holds a whole (series, head) and up to 288 rows
+// arrive at once, so the wait for them comes once (4096 series of 280 rows: 0.34
+// ms; four wavefronts in rounds, as the backward, 0.36).  Longer series take 8
 // wavefronts and 128 rows, which leave room for several workgroups on a CU (512
-// series of 1000 rows, forward / backward: 0.38 / 1.11 ms, and 0.42 / 1.20 with
-// 12 and 288); up to 128 rows 4 wavefronts waste none.
-enum AttnShape { kShort, kMiddle, kLong };
-inline AttnShape attn_shape(int64_t P, int T, dim3& grid, int& threads) {
+// series of 1000 rows: 0.37 ms, with 12 and 288 0.42); up to 128 rows 4 waste none.
+enum AttnFwd { kShort, kMiddle, kLong };
+inline AttnFwd attn_fwd_shape(int64_t P, int T, dim3& grid, int& threads) {
   const int n = (T + ATN - 1) / ATN;
-  const AttnShape sh = n <= 4 ? kShort : n <= 12 ? kMiddle : kLong;
+  const AttnFwd sh = n <= 4 ? kShort : n <= 12 ? kMiddle : kLong;
   const int w = sh == kShort ? 4 : sh == kMiddle ? (n + 3) / 4 * 4 : 8;
   threads = 64 * w;
   grid = dim3((unsigned)(P * NH * ((n + w - 1) / w)));
   return sh;
 }
 
+// Backward: four wavefronts, and up to 384 rows staged whole, once for all blocks
+// of a (series, head), which the wavefronts take in rounds.  Three or four such
+// workgroups share a CU, so that one's rows arrive while the others compute (4096
+// series of 280 rows: 0.80 ms; twelve wavefronts, one workgroup on a CU, with
+// transposed copies 1.10; the blocks over workgroups of one round each 0.95).
+// Below two workgroups for each CU (256 series of two heads) a round each keeps
+// the chip busy instead (64 series: 27 for 38 us).  Longer series as the forward.
+struct AttnBwd {
+  unsigned grid;
+  int ch, rounds;
+};
+inline AttnBwd attn_bwd_shape(int64_t P, int T) {
+  const int n = (T + ATN - 1) / ATN, w = n <= 12 ? 4 : 8;
+  const int rounds = n <= 12 && P * NH >= 512 ? (n + w - 1) / w : 1, per = w * rounds;
+  return AttnBwd{(unsigned)(P * NH * ((n + per - 1) / per)), n <= 4 ? 128 : n <= 9 ? 288 : n <= 12 ? 384 : 0, rounds};
+}
+
 template <int W, int CH>
-void attn_bwd(dim3 grid, int threads, hipStream_t s, const uint16_t* qkv, const uint16_t* o, const uint16_t* go,
-                     const float* lse, int T, uint16_t* dqkv) {
-  hipLaunchKernelGGL((k_attn_bwd_kv<W, CH>), grid, dim3(threads), 0, s, qkv, o, go, lse, T, dqkv);
-  hipLaunchKernelGGL((k_attn_bwd_q<W, CH>), grid, dim3(threads), 0, s, qkv, o, go, lse, T, dqkv);
+void attn_bwd(const AttnBwd& a, hipStream_t s, const uint16_t* qkv, const uint16_t* o, const uint16_t* go,
+              const float* lse, int T, uint16_t* dqkv) {
+  hipLaunchKernelGGL((k_attn_bwd_kv<W, CH>), dim3(a.grid), dim3(64 * W), 0, s, qkv, o, go, lse, T, a.rounds, dqkv);
+  hipLaunchKernelGGL((k_attn_bwd_q<W, CH>), dim3(a.grid), dim3(64 * W), 0, s, qkv, o, go, lse, T, a.rounds, dqkv);
 }
 
 // ---------------------------------------------------------------------------
@@ -1134,7 +1204,7 @@ int whs_tf_attn_fwd(const uint16_t* qkv, int64_t P, int T, uint16_t* o, float* l
   if (P == 0) return 0;
   dim3 grid;
   int threads;
-  switch (attn_shape(P, T, grid, threads)) {
+  switch (attn_fwd_shape(P, T, grid, threads)) {
     case kShort: hipLaunchKernelGGL((k_attn_fwd<4, 128>), grid, dim3(threads), 0, hs(stream), qkv, T, o, lse); break;
     case kMiddle: hipLaunchKernelGGL((k_attn_fwd<12, 288>), grid, dim3(threads), 0, hs(stream), qkv, T, o, lse); break;
     default: hipLaunchKernelGGL((k_attn_fwd<8, 128>), grid, dim3(threads), 0, hs(stream), qkv, T, o, lse); break;
@@ -1146,12 +1216,12 @@ int whs_tf_attn_bwd(const uint16_t* qkv, const uint16_t* o, const uint16_t* go, 
                     int T, uint16_t* dqkv, void* stream) {
   if (!qkv || !o || !go || !lse || !dqkv || P < 0 || T < 1 || T > MAXT) return -1;
   if (P == 0) return 0;
-  dim3 grid;
-  int threads;
-  switch (attn_shape(P, T, grid, threads)) {
-    case kShort: attn_bwd<4, 128>(grid, threads, hs(stream), qkv, o, go, lse, T, dqkv); break;
-    case kMiddle: attn_bwd<12, 288>(grid, threads, hs(stream), qkv, o, go, lse, T, dqkv); break;
-    default: attn_bwd<8, 128>(grid, threads, hs(stream), qkv, o, go, lse, T, dqkv); break;
+  const AttnBwd a = attn_bwd_shape(P, T);
+  switch (a.ch) {
+    case 128: attn_bwd<4, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
+    case 288: attn_bwd<4, 288>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
+    case 384: attn_bwd<4, 384>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
+    default: attn_bwd<8, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
   }
   return st(hipGetLastError());
 }
