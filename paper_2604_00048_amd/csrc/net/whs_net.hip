@@ -26,6 +26,14 @@ constexpr int HALO = 4;  // zero padding on each side
 constexpr int TM = 64;   // output time rows per tile
 
 // float -> bfloat16 bits, round to nearest even (gfx950 converts in one instruction)
+// two at once (one instruction for the pair)
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+}
+// max(v, 0), 0 for a NaN, in one instruction (a plain maximum first quiets v)
+__device__ __forceinline__ float relu(float v) { return __builtin_amdgcn_fmed3f(0.f, v, __builtin_inff()); }
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 
@@ -210,6 +218,28 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t* __restrict__ in, c
   }  // tiles
 }
 
+// The tiles of a workgroup: number tix = blockIdx.x, + gridDim.x, ..., of `per` to
+// a series.  Series and place are carried along: a 64-bit division is some 130
+// scalar instructions, and one for each store of a tile kept the matrix cores
+// waiting (the 64-to-64 layers below spent nine a tile).
+struct TileWalk {
+  int64_t tix, p;  // tile, series
+  int k, dk;       // place in the series, and the step's
+  int64_t dp;
+  __device__ __forceinline__ TileWalk(int per)
+      : tix(blockIdx.x), p(blockIdx.x / (unsigned)per), k((int)(blockIdx.x % (unsigned)per)),
+        dk((int)(gridDim.x % (unsigned)per)), dp(gridDim.x / (unsigned)per) {}
+  __device__ __forceinline__ void next(int per) {
+    tix += gridDim.x;
+    p += dp;
+    k += dk;
+    if (k >= per) {
+      k -= per;
+      ++p;
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // The 64-in, 64-out layers (MODE 0: + bias, ReLU; MODE 3: input gradient,
 // out kept where its ReLU bit is set) as out^T = W . window on
@@ -281,10 +311,6 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   }
   if (threadIdx.x < C) sbias[threadIdx.x] = (MODE == 0 && bias) ? bias[threadIdx.x] : 0.f;
 
-  auto tile_of = [&](int64_t tix, int64_t& p, int& t0) {
-    p = tix / ntiles;
-    t0 = (int)(tix - p * ntiles) * TR64;
-  };
   // rows [r0, r0 + nrows) of a series (row r0 + r -> LDS row r) into an LDS
   // buffer: load i covers LDS rows 8i .. 8i+7; lane L fills slot L & 7 of row
   // 8i + (L >> 3) with chunk (L & 7) ^ ((row >> 1) & 7)
@@ -297,10 +323,9 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * i), 16, off, 0, 0, 0);
     }
   };
-  auto fetch = [&](int64_t tix, unsigned char* dst, unsigned char* bdst) {
-    int64_t p;
-    int t0;
-    tile_of(tix, p, t0);
+  auto fetch = [&](const TileWalk& tw, unsigned char* dst, unsigned char* bdst) {
+    const int64_t p = tw.p;
+    const int t0 = tw.k * TR64;
     dma_rows(in + p * (int64_t)T * C, t0 - HALO, ROWS, dst);
     if constexpr (MODE == 3) {
       // 8 bytes per row, loaded as dwords (T * 8 is a whole number of them, so
@@ -312,11 +337,8 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
                                                  (uint32_t)(t0 * 8 + 256 * i + 4 * lane), 0, 0, 0);
     }
   };
-  // chunk q (of TR64 * 8 / 256) of the output tile of tile tix -> HBM
-  auto store_chunk = [&](int64_t tix, int q) {
-    int64_t p;
-    int t0;
-    tile_of(tix, p, t0);
+  // chunk q (of TR64 * 8 / 256) of the output tile at row t0 of series p -> HBM
+  auto store_chunk = [&](int64_t p, int t0, int q) {
     const int i = (int)threadIdx.x + 256 * q;
     const int r = i >> 3, c8 = i & 7;
     const int t = t0 + r;
@@ -328,16 +350,18 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   constexpr int NSTORE = TR64 * 8 / 256;  // output chunks per thread
   static_assert(NSTORE <= KT * C / 16, "the stores ride on the first K steps");
   // one tile from window buffer cur while the next tile's window loads into nxt
-  int64_t prev = -1;
-  auto step = [&](int64_t tix, const unsigned char* cur, unsigned char* nxt, const unsigned char* bcur,
+  int64_t prev = -1;  // the previous tile's series and first row
+  int prev_t0 = 0;
+  TileWalk tw(ntiles);  // the tile to fetch
+  auto step = [&](const unsigned char* cur, unsigned char* nxt, const unsigned char* bcur,
                   unsigned char* bnxt) {
-    int64_t p;
-    int t0;
-    tile_of(tix, p, t0);
+    const int64_t p = tw.p;
+    const int t0 = tw.k * TR64;
     // this tile's window and the previous tile's stores have landed
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0)
     __syncthreads();
-    if (tix + gridDim.x < total) fetch(tix + gridDim.x, nxt, bnxt);
+    tw.next(ntiles);
+    if (tw.tix < total) fetch(tw, nxt, bnxt);
 
     // MODE 0: the sums start from the bias of the accumulator's channel
     f32x16 acc[2][2];  // [row block][channel half]
@@ -374,7 +398,7 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
     for (int s = 0; s < NS; ++s) {
       if (s + 2 < NS) read_b(s + 2, vb[(s + 2) % 3]);
       // the previous tile's output leaves while the products run
-      if (s < NSTORE && prev >= 0) store_chunk(prev, s);
+      if (s < NSTORE && prev >= 0) store_chunk(prev, prev_t0, s);
 #pragma unroll
       for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -390,9 +414,13 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
       const int row = 64 * wave + 32 * m + l32;
-      // MODE 3: this row's 64 bits (bit c: channel c kept)
-      uint64_t rb = 0;
-      if constexpr (MODE == 3) rb = *reinterpret_cast<const uint64_t*>(bcur + 8 * row);
+      // MODE 3: this row's 64 bits (bit c: channel c kept), the lane's from bit 0 on
+      uint32_t rb[2] = {0u, 0u};
+      if constexpr (MODE == 3) {
+        const u32x2 r = *reinterpret_cast<const u32x2*>(bcur + 8 * row);
+        rb[0] = r[0] >> (4 * hi);
+        rb[1] = r[1] >> (4 * hi);
+      }
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -400,33 +428,33 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
           const int c0 = 32 * h + 8 * q + 4 * hi;  // first of the 4 channels
           float v[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = acc[m][h][4 * q + e];
-            if (MODE == 0) v[e] = v[e] > 0.f ? v[e] : 0.f;
-          }
-          u32x2 pk = {(uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                      (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16)};
+          for (int e = 0; e < 4; ++e) v[e] = MODE == 0 ? relu(acc[m][h][4 * q + e]) : acc[m][h][4 * q + e];
+          u32x2 pk = {pack2(v[0], v[1]), pack2(v[2], v[3])};
           if constexpr (MODE == 3) {
             // the 4 bits of channels c0 .. c0 + 3, each widened to 16
-            const uint32_t nib = (uint32_t)(h ? (rb >> 32) : rb) >> (8 * q + 4 * hi);
-            pk[0] &= (0u - (nib & 1u)) & 0xffffu | (0u - ((nib >> 1) & 1u)) << 16;
-            pk[1] &= (0u - ((nib >> 2) & 1u)) & 0xffffu | (0u - ((nib >> 3) & 1u)) << 16;
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+              const uint32_t lo = (uint32_t)__builtin_amdgcn_sbfe((int)rb[h], 8 * q + 2 * e, 1);
+              const uint32_t up = (uint32_t)__builtin_amdgcn_sbfe((int)rb[h], 8 * q + 2 * e + 1, 1);
+              pk[e] &= (lo & 0xffffu) | (up & 0xffff0000u);
+            }
           }
           *reinterpret_cast<u32x2*>(otile + row * OS + c0) = pk;
         }
     }
-    prev = tix;
+    prev = p;
+    prev_t0 = t0;
   };
 
-  if ((int64_t)blockIdx.x < total) fetch(blockIdx.x, win0, bits0);
-  for (int64_t tix = blockIdx.x; tix < total; tix += 2 * (int64_t)gridDim.x) {
-    step(tix, win0, win1, bits0, bits1);
-    if (tix + gridDim.x < total) step(tix + gridDim.x, win1, win0, bits1, bits0);
+  if (tw.tix < total) fetch(tw, win0, bits0);
+  while (tw.tix < total) {
+    step(win0, win1, bits0, bits1);
+    if (tw.tix < total) step(win1, win0, bits1, bits0);
   }
   if (prev >= 0) {
     __builtin_amdgcn_s_waitcnt(0x0070);  // every wave has written the last output tile
     __syncthreads();
-    for (int q = 0; q < NSTORE; ++q) store_chunk(prev, q);
+    for (int q = 0; q < NSTORE; ++q) store_chunk(prev, prev_t0, q);
   }
 }
 
@@ -534,19 +562,14 @@ __global__ __launch_bounds__(256, 1) void k_net_infer(const uint16_t* __restrict
     reinterpret_cast<uint32_t*>(bufB + NRI * 128)[i] = 0u;
   }
 
-  auto tile_of = [&](int64_t tix, int64_t& p, int& t0) {
-    p = tix / ntiles;
-    t0 = (int)(tix - p * ntiles) * TRI;
-  };
   // input rows day t0-16 .. into an input buffer (zero outside the series);
   // issued by every wavefront whether or not there is a tile (tix >= total
   // loads zeros through an empty range), so the wait counts are the same on
   // every path and waiting for other loads never waits for these
-  auto fetch = [&](int64_t tix, unsigned char* dst) {
-    int64_t p;
-    int t0;
-    const bool any = tix < total;
-    tile_of(any ? tix : 0, p, t0);
+  auto fetch = [&](const TileWalk& tw, unsigned char* dst) {
+    const bool any = tw.tix < total;
+    const int64_t p = any ? tw.p : 0;
+    const int t0 = any ? tw.k * TRI : 0;
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(in8 + p * (int64_t)T * 8), (short)0,
                                                       any ? T * 16 : 0, 0x00020000);
 #pragma unroll
@@ -579,17 +602,13 @@ __global__ __launch_bounds__(256, 1) void k_net_infer(const uint16_t* __restrict
     for (int b = 0; b < 2; ++b) {
       const int row = r0 + 32 * b + l32;
       const int t = t0 - off + row;
-      const bool in = t >= 0 && t < T;
+      const uint32_t in = t >= 0 && t < T ? ~0u : 0u;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         float v[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float a = acc[b][4 * q + e];
-          v[e] = (in && a > 0.f) ? a : 0.f;
-        }
-        const u32x2 pk = {(uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                          (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16)};
+        for (int e = 0; e < 4; ++e) v[e] = relu(acc[b][4 * q + e]);
+        const u32x2 pk = {pack2(v[0], v[1]) & in, pack2(v[2], v[3]) & in};
         const int c8 = 4 * chh + q;
         *reinterpret_cast<u32x2*>(dst + row * 128 + ((c8 ^ ((row >> 1) & 7)) << 4) + 8 * hi) = pk;
       }
@@ -623,26 +642,27 @@ __global__ __launch_bounds__(256, 1) void k_net_infer(const uint16_t* __restrict
   };
 
   float hprev = 0.f;
-  int64_t prev = -1;
+  int64_t prev = -1;  // the previous tile's series and first day
+  int prev_t0 = 0;
+  TileWalk tw(ntiles);  // the tile to fetch
   // h of the previous tile; a buffer store on every path (dropped through the
   // range where there is no row to write), like the loads above
   auto store_h = [&]() {
-    int64_t p;
-    int t0;
-    tile_of(prev >= 0 ? prev : 0, p, t0);
+    const int64_t p = prev >= 0 ? prev : 0;
+    const int t0 = prev_t0;
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(hout + p * (int64_t)T, (short)0, prev >= 0 ? T * 4 : 0,
                                                       0x00020000);
     const int t = t0 + (int)threadIdx.x;
     const uint32_t off = ((int)threadIdx.x < TRI && t < T) ? (uint32_t)t * 4u : 0x80000000u;
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(int, hprev), rs, off, 0, 0);
   };
-  auto step = [&](int64_t tix, const unsigned char* cur, unsigned char* nxt) {
-    int64_t p;
-    int t0;
-    tile_of(tix, p, t0);
+  auto step = [&](const unsigned char* cur, unsigned char* nxt) {
+    const int64_t p = tw.p;
+    const int t0 = tw.k * TRI;
     __builtin_amdgcn_s_waitcnt(0x0070);  // this tile's input and the previous tile's h stores have landed
     __syncthreads();
-    fetch(tix + gridDim.x, nxt);
+    tw.next(ntiles);
+    fetch(tw, nxt);
     store_h();
 
     f32x16 acc[2];
@@ -711,13 +731,14 @@ __global__ __launch_bounds__(256, 1) void k_net_infer(const uint16_t* __restrict
       for (int tap = 0; tap < KT; ++tap) h += ubuf[((int)threadIdx.x + tap) * 16 + tap];
       hprev = h;
     }
-    prev = tix;
+    prev = p;
+    prev_t0 = t0;
   };
 
-  fetch(blockIdx.x, inb0);
-  for (int64_t tix = blockIdx.x; tix < total; tix += 2 * (int64_t)gridDim.x) {
-    step(tix, inb0, inb1);
-    if (tix + gridDim.x < total) step(tix + gridDim.x, inb1, inb0);
+  fetch(tw, inb0);
+  while (tw.tix < total) {
+    step(inb0, inb1);
+    if (tw.tix < total) step(inb1, inb0);
   }
   __builtin_amdgcn_s_waitcnt(0x0070);  // the last (empty) input load before the kernel ends
   store_h();
@@ -811,7 +832,7 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ in, 
   const int g = lane >> 4;
   const int r16 = lane & 15;
   const int m = wave * 16 + r16;  // output channel of this lane's A row
-  const int64_t chunks = (T + TK - 1) / TK;
+  const int chunks = (T + TK - 1) / TK;
   const int64_t items = P * chunks;
 
   f32x4 acc[NT];
@@ -829,14 +850,15 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ in, 
   constexpr int XU = (TK / 2) * (CIN / 8), GU = (GR / 2) * (NOUT / 8);
   constexpr int UX = (XU + NTH - 1) / NTH, UG = (GU + NTH - 1) / NTH;  // units per thread
   u32x4 px0[UX], px1[UX], pg0[UG], pg1[UG];
-  auto fetch_item = [&](int64_t it) {
+  TileWalk tw(chunks);  // the item to load
+  auto fetch_item = [&]() {
 #pragma unroll
     for (int k = 0; k < UX; ++k) px0[k] = px1[k] = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
     for (int k = 0; k < UG; ++k) pg0[k] = pg1[k] = u32x4{0u, 0u, 0u, 0u};
-    if (it >= items) return;
-    const int64_t p = it / chunks;
-    const int t0 = (int)(it - p * chunks) * TK;
+    if (tw.tix >= items) return;
+    const int64_t p = tw.p;
+    const int t0 = tw.k * TK;
     const uint16_t* ip = in + p * (int64_t)T * CIN;
     const uint16_t* gp = gy + p * (int64_t)T * NOUT;
 #pragma unroll
@@ -858,9 +880,9 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ in, 
       if (t + 1 >= 0 && t + 1 < T) pg1[k] = *reinterpret_cast<const u32x4*>(gp + (int64_t)(t + 1) * NOUT + n0);
     }
   };
-  fetch_item(blockIdx.x);
+  fetch_item();
 
-  for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+  while (tw.tix < items) {
     __syncthreads();
     // the item's units into LDS: each stores 8 dwords, the (t, t+1) pair of one channel
 #pragma unroll
@@ -888,7 +910,8 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t* __restrict__ in, 
       }
     }
     __syncthreads();
-    fetch_item(it + gridDim.x);
+    tw.next(chunks);
+    fetch_item();
     // gradient window of this lane: rows 8g .. 8g+15 of channel m (taps cut 8 of them)
     uint32_t W[8];
 #pragma unroll
