@@ -1,10 +1,14 @@
 """The network's input and head for layouts of whole groups of 64 series go through
-LDS in tiles of 64 x 64; element for element they equal the series-contiguous form."""
+LDS in tiles of 64 x 64; element for element they equal the series-contiguous form.
+The weight gradient of a hidden layer takes items of 64 rows."""
 
+import numpy as np
 import pytest
 import torch
 
+from oracle import convnet_ref as N
 from paper_2604_00048_amd import net
+from tests.test_gpu_net import from_bf, rel, to_bf
 
 pytestmark = pytest.mark.gpu
 dev = "cuda"
@@ -40,3 +44,18 @@ def test_tiles_equal_the_contiguous_form(P, T, S, d):
     tiles = lam(S, nb).transpose(1, 2).reshape(nb * S, T - d)
     assert torch.equal(tiles[:P].view(torch.int32), rows.view(torch.int32))
     assert (tiles[P:] == -5.0).all()                  # rows past the batch are not written
+
+
+@pytest.mark.parametrize("P,T,parts", [(1, 1, 1), (3, 4, 2), (2, 59, 3), (5, 63, 4), (3, 64, 2), (4, 65, 9), (2, 128, 1),
+                                       (7, 133, 5)])
+def test_hidden_weight_gradient_at_the_edges_of_its_items(P, T, parts):
+    """Ends of a series inside the halo, items cut short, more workgroups than items; the
+    bar of the other shapes (FP32 sums of exact bfloat16 products)."""
+    r = np.random.default_rng(P * T)
+    x, gy = (N.bf16_round(r.normal(size=(P, T, 64))) for _ in range(2))
+    grad = torch.empty(64 * 9 * 64 + 64, dtype=torch.float32, device=dev)
+    net.conv_wgrad(to_bf(x), 64, to_bf(gy), 64, grad, P, T, parts=parts)
+    gW, gb = N.conv1d_wgrad(x, gy)
+    g = grad.cpu().double().numpy()
+    assert rel(g[:64 * 9 * 64].reshape(64, 9, 64), gW) < 1e-5
+    assert rel(g[64 * 9 * 64:], gb) < 1e-5
