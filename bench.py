@@ -547,7 +547,7 @@ def main():
     ap.add_argument("--interleave", type=int, default=64)
     ap.add_argument("--w-bits", action="store_true", help="heteroscedastic workload: weights packed eight to a byte")
     ap.add_argument("--in-place", action="store_true",
-                    help="interleave 1: read the contiguous layout in place instead of through interleaved copies")
+                    help="interleave 1: with the smaller workspace, which leaves no room for interleaved copies")
     ap.add_argument("--n-uneven", type=int, default=100000)
     ap.add_argument("--retune", action="store_true")
     ap.add_argument("--train-steps", type=int, default=400)
@@ -731,7 +731,7 @@ def bench_hetero(args):
                         + (", 0/1 weights packed eight to a byte" if args.w_bits else ""),
             "P": P, "T": T, "d": d, "C": 1, "storage": args.dtype, "interleave": S,
             **({"w_format": "bits"} if args.w_bits else {}),
-            **({"contiguous_path": "in place" if args.in_place else "interleaved copies"} if S == 1 else {}),
+            **({"contiguous_path": "smaller workspace" if args.in_place else "larger workspace"} if S == 1 else {}),
         },
         "roofline": {
             "bound": "hbm",
