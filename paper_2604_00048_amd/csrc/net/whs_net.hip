@@ -42,13 +42,11 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(fl
 // set where the value is > 0, which for these values (never negative) is where
 // its bits are not zero
 __device__ __forceinline__ uint8_t relu_bits(u32x4 v) {
-  uint32_t b = 0;
+  // adding 0x7fff carries into a half's top bit if it is not zero, and no further
+  uint32_t m = (v[0] + 0x7fff7fffu) & 0x80008000u;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    b |= min(v[q] & 0xffffu, 1u) << (2 * q);
-    b |= min(v[q] >> 16, 1u) << (2 * q + 1);
-  }
-  return (uint8_t)b;
+  for (int q = 1; q < 4; ++q) m = (m >> 2) | ((v[q] + 0x7fff7fffu) & 0x80008000u);
+  return (uint8_t)(m >> 9 | m >> 24);  // low halves at 9 + 2q, high halves at 25 + 2q
 }
 // keep the bfloat16 values of a 16-byte chunk whose bit is set, zero the rest
 __device__ __forceinline__ u32x4 apply_bits(u32x4 v, uint32_t m) {
@@ -312,22 +310,30 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   }
   if (threadIdx.x < C) sbias[threadIdx.x] = (MODE == 0 && bias) ? bias[threadIdx.x] : 0.f;
 
-  // rows [r0, r0 + nrows) of a series (row r0 + r -> LDS row r) into an LDS
-  // buffer: load i covers LDS rows 8i .. 8i+7; lane L fills slot L & 7 of row
-  // 8i + (L >> 3) with chunk (L & 7) ^ ((row >> 1) & 7)
-  auto dma_rows = [&](const uint16_t* series, int r0, int nrows, unsigned char* dst) {
+  // the window's rows t0 - HALO .. of a series into an LDS buffer: load i covers LDS
+  // rows 8i .. 8i+7; lane L fills slot L & 7 of row r = 8i + (L >> 3) with chunk
+  // (L & 7) ^ ((r >> 1) & 7).  A wavefront's loads lie 32 rows apart and share the
+  // permutation, so they differ by a scalar offset only; the first has an address of
+  // its own, since rows before the series (which wrap out of range) are told by it.
+  const int drow = 8 * wave + (lane >> 3);
+  const uint32_t dcol = (uint32_t)(((lane & 7) ^ ((drow >> 1) & 7)) * 16);
+  auto dma_window = [&](const uint16_t* series, int t0, unsigned char* dst) {
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(series), (short)0, T * 128, 0x00020000);
-    for (int i = wave; i < nrows / 8; i += 4) {
-      const int r = 8 * i + (lane >> 3);
-      const int chunk = (lane & 7) ^ ((r >> 1) & 7);
-      const uint32_t off = (uint32_t)((r0 + r) * 128 + chunk * 16);  // rows before 0 wrap out of range
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * i), 16, off, 0, 0, 0);
-    }
+    const uint32_t off = (uint32_t)((t0 - HALO + drow) * 128) + dcol;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * wave), 16, off, 0, 0, 0);
+#pragma unroll
+    for (int j = 1; j < ROWS / 32; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * wave + 4096 * j), 16, off + 4096u, 4096 * (j - 1),
+                                               0, 0);
+    if (wave == 0)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 4096 * (ROWS / 32)), 16, off + 4096u,
+                                               4096 * (ROWS / 32 - 1), 0, 0);
   };
+  static_assert(ROWS % 32 == 8, "the last 8 rows are one load of the first wavefront");
   auto fetch = [&](const TileWalk& tw, unsigned char* dst, unsigned char* bdst) {
     const int64_t p = tw.p;
     const int t0 = tw.k * TR64;
-    dma_rows(in + p * (int64_t)T * C, t0 - HALO, ROWS, dst);
+    dma_window(in + p * (int64_t)T * C, t0, dst);
     if constexpr (MODE == 3) {
       // 8 bytes per row, loaded as dwords (T * 8 is a whole number of them, so
       // the buffer range zeroes exactly the rows past the series)
@@ -338,15 +344,17 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
                                                  (uint32_t)(t0 * 8 + 256 * i + 4 * lane), 0, 0, 0);
     }
   };
-  // chunk q (of TR64 * 8 / 256) of the output tile at row t0 of series p -> HBM
+  // chunk q (of TR64 * 8 / 256, 32 rows each) of the output tile at row t0 of
+  // series p -> HBM, rows past the series dropped through the buffer range
+  const int srow = (int)threadIdx.x >> 3, sc8 = (int)threadIdx.x & 7;
   auto store_chunk = [&](int64_t p, int t0, int q) {
-    const int i = (int)threadIdx.x + 256 * q;
-    const int r = i >> 3, c8 = i & 7;
-    const int t = t0 + r;
-    if (t >= T) return;
-    u32x4 v = *reinterpret_cast<const u32x4*>(otile + r * OS + 8 * c8);
-    *reinterpret_cast<u32x4*>(out + (p * (int64_t)T + t) * C + 8 * c8) = v;
-    if (MODE == 0 && bits) bits[(p * (int64_t)T + t) * 8 + c8] = relu_bits(v);
+    const u32x4 v = *reinterpret_cast<const u32x4*>(otile + (srow + 32 * q) * OS + 8 * sc8);
+    const auto ro = __builtin_amdgcn_make_buffer_rsrc(out + p * (int64_t)T * C, (short)0, T * 128, 0x00020000);
+    __builtin_amdgcn_raw_buffer_store_b128(v, ro, (uint32_t)((t0 + srow) * 128 + 16 * sc8), 4096 * q, 0);
+    if (MODE == 0 && bits) {
+      const auto rb = __builtin_amdgcn_make_buffer_rsrc(bits + p * (int64_t)T * 8, (short)0, T * 8, 0x00020000);
+      __builtin_amdgcn_raw_buffer_store_b8(relu_bits(v), rb, (uint32_t)((t0 + srow) * 8 + sc8), 256 * q, 0);
+    }
   };
   constexpr int NSTORE = TR64 * 8 / 256;  // output chunks per thread
   static_assert(NSTORE <= KT * C / 16, "the stores ride on the first K steps");
