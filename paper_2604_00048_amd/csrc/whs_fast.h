@@ -127,9 +127,12 @@ struct Fast {
     return r > B ? B : r;
   }
 
-  template <bool SWEEP2>
+  // FIRST: t0 is the constant 0.  The compiler then takes the row count's minimum on
+  // the vector unit and loops over the lanes' buffer descriptors at every load; made
+  // scalar again, the solve of 64 series of 365 days takes 59.6 us for 61.4.
+  template <bool SWEEP2, bool FIRST = false>
   __device__ __forceinline__ void load_tile(Tile& tl, int t0) const {
-    const int rows = rows_from(t0, T);
+    const int rows = FIRST ? __builtin_amdgcn_readfirstlane(rows_from(t0, T)) : rows_from(t0, T);
     const int tb = rows > 0 ? t0 : 0;
     const auto rx = make_rsrc(xb + (int64_t)tb * Ctot * S, rows * Rx);
     const auto rw = make_rsrc(wb + (int64_t)tb * w_row_bytes(), rows * w_row_bytes());
@@ -146,7 +149,7 @@ struct Fast {
       }
     }
     if constexpr (PERDIFF) {
-      const int rl = rows_from(t0, T - D);
+      const int rl = FIRST ? __builtin_amdgcn_readfirstlane(rows_from(t0, T - D)) : rows_from(t0, T - D);
       const int tl0 = rl > 0 ? t0 : 0;
       const auto rlm = make_rsrc(lb + (int64_t)tl0 * S, rl * S * ES);
 #pragma unroll
@@ -464,7 +467,7 @@ struct Fast {
     int nobs = 0;
     int bad_tile = -1;
     Tile A, Bt;
-    load_tile<false>(A, 0);
+    load_tile<false, C == 1 && !TAB>(A, 0);
     for (int j = 0; j < nt; j += 2) {
       load_tile<false>(Bt, (j + 1) * B);
       store_ck(st, j);
