@@ -220,7 +220,9 @@ __global__ __launch_bounds__(256) void k_conv(const uint16_t* __restrict__ in, c
 // The tiles of a workgroup: number tix = blockIdx.x, + gridDim.x, ..., of `per` to
 // a series.  Series and place are carried along: a 64-bit division is some 130
 // scalar instructions, and one for each store of a tile kept the matrix cores
-// waiting (the 64-to-64 layers below spent nine a tile).
+// waiting (the 64-to-64 layers below spent nine a tile: 1.15 ms forward on 4096
+// series of 3288 days, 1.07 without; the fused inference of 8192, three, 5.33 and
+// 4.71 ms).
 struct TileWalk {
   int64_t tix, p;  // tile, series
   int k, dk;       // place in the series, and the step's
@@ -266,6 +268,11 @@ struct TileWalk {
 // ReLU bits as the tile is stored.
 // LDS rows are 128 B with the 16-byte chunks of row r permuted by XOR with
 // (r >> 1) & 7, so the 16 rows read by a quarter wavefront hit distinct banks.
+// Bound by the matrix cores, busy about half the cycles, and by what the one
+// wavefront of a SIMD issues between a tile's last product and the next one's first:
+// so rounding goes two values at once, ReLU is one instruction, and stores and loads
+// of a tile differ by a scalar offset.  4096 series of 3288 days: forward 0.96 ms,
+// 1040 TFLOP/s, input gradient 1.05 (one value and one address at a time 1.07, 1.09).
 // ---------------------------------------------------------------------------
 constexpr int TR64 = 256;  // time rows per tile of the 64-to-64 layers
 
