@@ -276,6 +276,18 @@ struct TileWalk {
 // ---------------------------------------------------------------------------
 constexpr int TR64 = 256;  // time rows per tile of the 64-to-64 layers
 
+// The rows of a series from r on (T - r of them, none if r is past its end) as a buffer
+// range; n values to a row.  A tile's loads and stores lie whole groups of rows apart:
+// they share the lanes' offsets and differ by their range, which ends at the series'
+// end for each.  (The scalar operand of the instruction could hold the distance
+// instead, but it is not part of the offset that the range is checked against.)
+template <typename V>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const V* series, int T, int r, int n) {
+  const int left = T > r ? T - r : 0;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<V*>(series) + (int64_t)r * n, (short)0, left * n * (int)sizeof(V),
+                                           0x00020000);
+}
+
 template <int MODE>
 __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ in, const uint16_t* __restrict__ wt,
                                                    const float* __restrict__ bias, const void* __restrict__ maskv,
@@ -320,21 +332,20 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   // the window's rows t0 - HALO .. of a series into an LDS buffer: load i covers LDS
   // rows 8i .. 8i+7; lane L fills slot L & 7 of row r = 8i + (L >> 3) with chunk
   // (L & 7) ^ ((r >> 1) & 7).  A wavefront's loads lie 32 rows apart and share the
-  // permutation, so they differ by a scalar offset only; the first has an address of
-  // its own, since rows before the series (which wrap out of range) are told by it.
+  // permutation; the first has an address of its own, since rows before the series
+  // (which wrap out of range) are told by it.
   const int drow = 8 * wave + (lane >> 3);
-  const uint32_t dcol = (uint32_t)(((lane & 7) ^ ((drow >> 1) & 7)) * 16);
+  const uint32_t doff = (uint32_t)(drow * 128 + ((lane & 7) ^ ((drow >> 1) & 7)) * 16);
   auto dma_window = [&](const uint16_t* series, int t0, unsigned char* dst) {
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(series), (short)0, T * 128, 0x00020000);
-    const uint32_t off = (uint32_t)((t0 - HALO + drow) * 128) + dcol;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * wave), 16, off, 0, 0, 0);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, 0, C), (lptr)(dst + 1024 * wave), 16,
+                                             doff + (uint32_t)((t0 - HALO) * 128), 0, 0, 0);
 #pragma unroll
     for (int j = 1; j < ROWS / 32; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * wave + 4096 * j), 16, off + 4096u, 4096 * (j - 1),
-                                               0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, t0 - HALO + 32 * j, C),
+                                               (lptr)(dst + 1024 * wave + 4096 * j), 16, doff, 0, 0, 0);
     if (wave == 0)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 4096 * (ROWS / 32)), 16, off + 4096u,
-                                               4096 * (ROWS / 32 - 1), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, t0 - HALO + ROWS / 32 * 32, C),
+                                               (lptr)(dst + 4096 * (ROWS / 32)), 16, doff, 0, 0, 0);
   };
   static_assert(ROWS % 32 == 8, "the last 8 rows are one load of the first wavefront");
   auto fetch = [&](const TileWalk& tw, unsigned char* dst, unsigned char* bdst) {
@@ -356,12 +367,11 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   const int srow = (int)threadIdx.x >> 3, sc8 = (int)threadIdx.x & 7;
   auto store_chunk = [&](int64_t p, int t0, int q) {
     const u32x4 v = *reinterpret_cast<const u32x4*>(otile + (srow + 32 * q) * OS + 8 * sc8);
-    const auto ro = __builtin_amdgcn_make_buffer_rsrc(out + p * (int64_t)T * C, (short)0, T * 128, 0x00020000);
-    __builtin_amdgcn_raw_buffer_store_b128(v, ro, (uint32_t)((t0 + srow) * 128 + 16 * sc8), 4096 * q, 0);
-    if (MODE == 0 && bits) {
-      const auto rb = __builtin_amdgcn_make_buffer_rsrc(bits + p * (int64_t)T * 8, (short)0, T * 8, 0x00020000);
-      __builtin_amdgcn_raw_buffer_store_b8(relu_bits(v), rb, (uint32_t)((t0 + srow) * 8 + sc8), 256 * q, 0);
-    }
+    __builtin_amdgcn_raw_buffer_store_b128(v, rows_from(out + p * (int64_t)T * C, T, t0 + 32 * q, C),
+                                           (uint32_t)(srow * 128 + 16 * sc8), 0, 0);
+    if (MODE == 0 && bits)
+      __builtin_amdgcn_raw_buffer_store_b8(relu_bits(v), rows_from(bits + p * (int64_t)T * 8, T, t0 + 32 * q, 8),
+                                           (uint32_t)(srow * 8 + sc8), 0, 0);
   };
   constexpr int NSTORE = TR64 * 8 / 256;  // output chunks per thread
   static_assert(NSTORE <= KT * C / 16, "the stores ride on the first K steps");
