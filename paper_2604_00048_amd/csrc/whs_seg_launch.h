@@ -13,16 +13,16 @@ constexpr int kCus = 256;  // MI355X
 
 // Steps per tile.  One band: as the one-lane kernel's in FP32 storage; the
 // adjoint of order 2 takes 22 (24 spilled 260 bytes per lane).  Several bands
-// run in groups of 3 (solve) or 2 (adjoint) and one: the widest groups whose
+// (MB) run in groups of 3 (solve) or 2 (adjoint) and fewer: the widest groups whose
 // tiles stay deep enough for the checkpoints to cost less than the weights and
 // the mask read again, and free of spills (3 bands of the adjoint at 12 steps
-// spilled 232 bytes per lane).  The checkpoints (seg_fields per tile, none for a
-// segment's first) stay below what checkpoint_bytes reports for the call: in
-// doubles per step at order 2, 9 / 22 against 5 / 12 for one band, 11 / 13
-// against 7 / 8 for two, 13 / 16 against 9 / 8 for three; at order 1, 3 / 24
-// against 2 / 16, 4 / 13 against 3 / 8, 5 / 16 against 4 / 8.
-template <int D, int C, bool BWD>
-constexpr int seg_tile() { return C == 1 ? (D == 2 && BWD ? 22 : 24) : BWD ? 13 : 16; }
+// spilled 232 bytes per lane).  Every group of a call takes the same tile: its
+// segments then end at the same rows, and every group factors a series alike and
+// agrees on whether it is singular.  (That costs a last band alone some checkpoints,
+// its tile would else be 24 and 22: ten bands of 16,384 series of 3288 days, solve
+// and adjoint, 4.13 -> 4.16 ms.)
+template <int D, int C, bool BWD, bool MB>
+constexpr int seg_tile() { return !MB ? (D == 2 && BWD ? 22 : 24) : BWD ? 13 : 16; }
 
 constexpr int seg_group(int bands, bool bwd) {
   const int widest = bwd ? 2 : 3;
@@ -59,17 +59,22 @@ inline bool seg_shape(const LaunchDesc& L, SegShape& s) {
 template <int D, bool BWD>
 inline size_t seg_contiguous_bytes(const LaunchDesc& L) {
   SegShape s;
-  if (!seg_shape<seg_tile<D, 1, BWD>()>(L, s)) return ~(size_t)0;
+  if (!seg_shape<seg_tile<D, 1, BWD, false>()>(L, s)) return ~(size_t)0;
   const size_t lanes = (size_t)s.groups * ((size_t)s.nseg << s.sw_log2);
   return lanes * ((size_t)(s.tps - 1) * seg_fields<D, 1>() * sizeof(double) + (size_t)s.tps * 4);
 }
 
 template <int D, int C, bool BWD, bool PERDIFF, bool WB, bool MB, bool CT = false>
 hipError_t launch_seg_group(const LaunchDesc& L, int c0, hipStream_t stream) {
-  constexpr int B = seg_tile<D, C, BWD>();
-  // (tps - 1) nseg < T / B checkpoints of seg_fields, against the T / 12 (one
-  // band, uneven dates) or T / 8 tiles of the same group that size the workspace
-  static_assert(seg_fields<D, C>() * (C == 1 ? tile_depth<D, 1, true>() : tile_depth<D, C>()) <= ck_fields<D, C>() * B,
+  constexpr int B = seg_tile<D, C, BWD, MB>();
+  // The checkpoints fit the workspace of an interleaved call: (tps - 1) nseg < T / B
+  // of seg_fields against the T / 12 (one band, uneven dates) or, as a call of several
+  // bands always has a group of two, T / 8 tiles that size it.  In doubles per step
+  // at order 2, 9 / 22 against 5 / 12 for one band; 13 / 16 (three), 11 / 13 (two)
+  // and 9 / 13 (a last one) against 7 / 8; at order 1, 3 / 24 against 2 / 16, and
+  // 5 / 16, 4 / 13 and 3 / 13 against 3 / 8.
+  static_assert(MB ? seg_fields<D, C>() * tile_depth<D, 2>() <= ck_fields<D, 2>() * B
+                   : seg_fields<D, C>() * tile_depth<D, 1, true>() <= ck_fields<D, 1>() * B,
                 "the checkpoints must fit the workspace of an interleaved call");
   SegShape s;
   if (!seg_shape<B>(L, s)) return hipErrorInvalidValue;
