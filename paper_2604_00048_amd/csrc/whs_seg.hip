@@ -35,6 +35,31 @@ hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 // order of elimination changes on ill-conditioned series; the one-band solve with
 // a weight per series below 512 steps, which gives bit for bit what a plan's
 // launch of one lane per series gives for that group; order 3 and 4, whose state leaves no registers for the spike.
+// Several bands: the segments take 3 (solve) or 2 (adjoint) to a launch, one lane
+// per series 5 or 3 (solve) and 3, and every launch factors the series again.  With
+// eight segments and more that never matters; with fewer the segments' time grows
+// with the launches and the series while one lane per series waits the same time
+// for any batch, so they are taken where their launches are few enough.  Times of
+// one lane per series over those of the segments, lengths of 100 to 1000 steps:
+//   two segments (20,000 and 32,768 series)
+//     solve    a weight per series 1.08-1.43; per difference row, twice the launches
+//              or more (4, 5, 10 bands) 0.83-1.23, fewer 1.01-1.55
+//     adjoint  as many launches (2, 4 bands) 1.00-1.71; up to 1.33 times (7, 8, 10)
+//              1.01-1.41, but 0.89-1.15 at order 1 with a weight per series; more (3,
+//              5, 6, 9, 12) 0.61-1.24
+//   four segments (16,384 series)
+//     adjoint  three bands, a weight per difference row 0.90-1.14, others 1.16-2.58
+static bool bands_pay(const LaunchDesc& L, bool bwd) {
+  SegShape s;
+  if (bwd ? !seg_shape<seg_tile<2, 2, true, true>()>(L, s) : !seg_shape<seg_tile<2, 2, false, true>()>(L, s)) return false;
+  if (s.nseg > 4) return true;
+  const int widest = seg_group(L.C, bwd), one_lane = max_group(L.D, bwd, false, L.perdiff);
+  const int n = (L.C + widest - 1) / widest, n1 = (L.C + one_lane - 1) / one_lane;
+  if (!bwd) return s.nseg > 2 || n < 2 * n1;
+  if (s.nseg > 2) return !L.perdiff || n < 2 * n1;
+  return L.D == 1 && !L.perdiff ? n <= n1 : 2 * n < 3 * n1;
+}
+
 bool seg_path(const LaunchDesc& L, bool bwd) {
   if (L.fac || L.coef || L.f64 || L.D > 2 || L.T < 96 || L.P < 1 || L.P >= ((int64_t)1 << 31))
     return false;
@@ -43,7 +68,7 @@ bool seg_path(const LaunchDesc& L, bool bwd) {
   if ((int64_t)L.T * L.C * 256 >= ((int64_t)1 << 30)) return false;  // 32-bit offsets, tiles past the end included
   SegShape s;
   if (!seg_shape<24>(L, s)) return false;
-  if (L.S == 64) return true;
+  if (L.S == 64) return L.C == 1 || bands_pay(L, bwd);
   // up to 1024 series the partition kernel's 256 lanes per series are ahead (64
   // series 25 / 27 us against 54 / 70, 1024 series 70 / 80 against 62 / 100); a
   // call with the larger workspace keeps the interleaved call's results bit for bit

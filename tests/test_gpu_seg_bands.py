@@ -1,13 +1,16 @@
 """Several bands in segments: the launches of one call (3 and fewer bands of a solve,
 2 and fewer of an adjoint) factor a series in the same segments, so they agree on
-which series are singular to working precision."""
+which series are singular to working precision; and two and four segments, where the
+number of bands, the order and the weights decide between segments and one lane per
+series."""
 
 import numpy as np
 import pytest
 import torch
 
 from paper_2604_00048_amd import synth, whs
-from tests._cases import from_device_rows, from_device_series, to_device
+from tests._cases import from_device_rows, from_device_series, random_case, to_device
+from tests.test_gpu_seg import _check
 
 pytestmark = pytest.mark.gpu
 
@@ -46,3 +49,12 @@ def test_bands_agree_on_singular_series(P, T, d, C):
     gl = np.isnan(from_device_rows(gl, P).reshape(P, -1))
     np.testing.assert_array_equal(gl.all(1), gbad)
     np.testing.assert_array_equal(gl.any(1), gbad)
+
+
+@pytest.mark.parametrize("P,T,d,C,per_diff", [
+    (16385, 131, 2, 2, True), (16451, 400, 1, 3, False), (20001, 100, 2, 4, False), (20001, 97, 1, 4, False),
+    (32768, 97, 2, 7, True), (16400, 150, 1, 10, True), (16390, 96, 2, 5, True), (8193, 120, 2, 3, True), (16384, 113, 1, 4, True),
+])
+def test_bands_in_two_and_four_segments(P, T, d, C, per_diff):
+    x, w, lam = random_case(P, T, d, C=C, per_diff=per_diff, seed=P + T + C, dtype=torch.float32, p_obs=0.1)
+    _check(x, w, lam, d, P, rows=np.r_[0:3, P // 2:P // 2 + 3, P - 3:P])
