@@ -27,8 +27,8 @@ hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 // turned through LDS, instead of three copies into the interleaved layout and
 // back (or, for small batches, the partition kernel):
 //       64 series   611 /  812 ->  54 /  70      16,384 series   958 / 1315 ->  383 /  620
-//    4,096 series   706 /  951 -> 120 / 213      65,536 series  2094 / 3088 -> 1523 / 2477
-// (interleaved, 103 / 146 and 281 / 393 at 4096 and 16,384: a lane's pieces of 88
+//    4,096 series   706 /  951 -> 120 / 213      65,536 series  2091 / 3093 -> 1532 / 2484
+// (the last in one segment; interleaved, 103 / 146 and 281 / 393 at 4096 and 16,384: a lane's pieces of 88
 // to 96 bytes split lines of 128, and the lines that 65,536 lanes hold open in
 // five arrays exceed the L2).
 // Not taken: FP64 storage, whose callers see the last digits, which another

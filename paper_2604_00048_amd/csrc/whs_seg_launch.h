@@ -36,14 +36,15 @@ struct SegShape {
 
 // As many segments as leave every wavefront its own SIMD (1024 on the chip) and
 // every segment a tile: 32 for up to 2048 series, then 16, 8, 4 and, up to
-// 32,768 series, 2 (beyond, one lane per series fills the chip by itself; series-
-// contiguous batches stay with 2, which still saves them the copies).
+// 32,768 series, 2.  Beyond, one lane per series fills the chip by itself.  Series-
+// contiguous batches then take one segment, which saves them the copies and is the
+// recurrence of one lane per series: the two layouts give the same results at every size.
 template <int B>
 inline bool seg_shape(const LaunchDesc& L, SegShape& s) {
   const int nt = (L.T + B - 1) / B;
-  for (s.sw_log2 = 3, s.nseg = 32; s.nseg >= 2; s.nseg /= 2) {
+  for (s.sw_log2 = 3, s.nseg = 32; s.nseg >= (L.S == 1 ? 1 : 2); s.nseg /= 2) {
     s.groups = (L.P + (1 << s.sw_log2) - 1) >> s.sw_log2;
-    const bool room = (s.groups << s.sw_log2) * s.nseg <= kCus * 4 * 64 || (L.S == 1 && s.nseg == 2);
+    const bool room = (s.groups << s.sw_log2) * s.nseg <= kCus * 4 * 64 || s.nseg == 1;
     if (room && s.nseg <= nt) {
       s.tps = (nt + s.nseg - 1) / s.nseg;
       s.ne = (nt + s.tps - 1) / s.tps;
@@ -100,8 +101,11 @@ hipError_t launch_seg_group(const LaunchDesc& L, int c0, hipStream_t stream) {
   g.nseg = s.nseg;
   g.tps = s.tps;
   g.ne = s.ne;
-  // two segments of 64 series make two wavefronts, every other shape four
-  if (s.nseg == 2)
+  // one or two segments of 64 series make as many wavefronts, every other shape four
+  if (CT && s.nseg == 1)
+    hipLaunchKernelGGL((k_seg<D, C, B, float, BWD, PERDIFF, WB, CT ? 64 : 128, MB, CT>), dim3((unsigned)s.groups),
+                       dim3(64), 0, stream, g);
+  else if (s.nseg == 2)
     hipLaunchKernelGGL((k_seg<D, C, B, float, BWD, PERDIFF, WB, 128, MB, CT>), dim3((unsigned)s.groups), dim3(128), 0,
                        stream, g);
   else
