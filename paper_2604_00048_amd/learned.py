@@ -24,6 +24,7 @@ from . import net, synth, whs
 D = 2
 S = 64                # interleave of the evaluation chunks (one lane per series fills the chip)
 SMALL_BATCH = 8192    # training batches up to this size are series-contiguous
+PARTITION_BATCH = 1024  # and up to this one run the smoother on the partition kernel
 T_DAYS = 3288
 GRID = [10.0 ** (-1.0 + 0.3 * i) for i in range(21)]
 
@@ -35,6 +36,16 @@ def layout_for(P: int) -> int:
     series-contiguous tensors (interleave 1) the network's input and head kernels
     read coalesced."""
     return 1 if P <= SMALL_BATCH else S
+
+
+def staged_for(P: int) -> bool:
+    """``staged`` of a training batch's smoother calls.  The smallest batches take the
+    partition kernel, which the smaller workspace selects: 256 lanes per series against
+    the segments' 32 (solve and adjoint of 3288 days: 64 series 52 us against 121, 500
+    series 70 against 139, 1024 series 148 against 155).  From 1100 series on (187
+    against 157) the segments are ahead, whose adjoint needs the larger workspace:
+    328 MB for 4096 series, of which the segments use 45."""
+    return P > PARTITION_BATCH
 
 
 @dataclass
@@ -104,11 +115,12 @@ class Learned:
 
     def train_step(self, batch: Batch, lr: float) -> float:
         h, lam = self.weights(batch, keep=True)
-        z, info = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P)
+        z, info = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P, staged=staged_for(batch.P))
         loss = torch.zeros(1, dtype=torch.float64, device=self.device)
         # MSE in standardised units: (z - x)^2 / sd^2 averaged over held-out points
         g = net.mse(z, batch.x_true, batch.hold, 1.0 / (max(batch.n_hold, 1) * self.sd ** 2), loss=loss)
-        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False)
+        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False,
+                                       staged=staged_for(batch.P))
         gh = net.head_bwd1(h, glam, batch.P, T_DAYS, batch.S, D)
         self.model.backward1(gh, batch.P, T_DAYS)
         self.model.adam(lr)
@@ -131,10 +143,11 @@ class LearnedScalar:
 
     def train_step(self, batch: Batch, lr: float, sd: float) -> float:
         lam = self.weights(batch)
-        z, _ = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P)
+        z, _ = whs.whs_solve(batch.x_train, batch.w_train, lam, D, batch.P, staged=staged_for(batch.P))
         loss = torch.zeros(1, dtype=torch.float64, device=self.device)
         g = net.mse(z, batch.x_true, batch.hold, 1.0 / (max(batch.n_hold, 1) * sd ** 2), loss=loss)
-        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False)
+        _, glam, _ = whs.whs_backward(batch.w_train, lam, z, g, D, batch.P, need_x=False,
+                                       staged=staged_for(batch.P))
         gt = net.scalar_head_bwd(self.theta, glam, batch.P)
         self.step += 1
         net._chk(net.lib().whs_net_adam(net._p(self.theta), net._p(gt), net._p(self.m), net._p(self.v), 1, lr, 0.9,
