@@ -35,8 +35,10 @@ static hipError_t gcv_go(const GcvLaunch& L, hipStream_t stream) {
   const int per_wave = 64 >> SL;
   const int waves = ((L.n_grid + G - 1) / G + per_wave - 1) / per_wave;
   const int passes = (waves + NT / 64 - 1) / (NT / 64);
-  const int threads = 64 * ((waves + passes - 1) / passes);
+  int threads = 64 * ((waves + passes - 1) / passes);
   const int64_t blocks = (L.P + (1 << SL) - 1) >> SL;
+  // a launch holds fewer than 2^32 work-items: beyond, one wavefront takes all passes
+  if (blocks * threads >= (int64_t)1 << 32) threads = 64;
   hipLaunchKernelGGL((k_gcv<D, kGcvTile, TS, G, SL, NT, W>), dim3((unsigned)blocks), dim3(threads), 0, stream, a);
   return hipGetLastError();
 }
