@@ -1,5 +1,6 @@
-"""GCV of more series than a launch has work-items for with several wavefronts to a block
-of 64 series (614,400,000 series of 21 values at order 3)."""
+"""GCV of large batches: grids whose passes one wavefront takes for a block of 64 series at
+sizes where the 21-value grid is spread over several; and more series than a launch has
+work-items for with several wavefronts to a block (614,400,000 of 21 values at order 3)."""
 
 import numpy as np
 import pytest
@@ -7,8 +8,15 @@ import torch
 
 from oracle import whs_ref as R
 from paper_2604_00048_amd import whs
+from tests import test_gpu_gcv_forms as forms
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt", [torch.float64, torch.float32])
+@pytest.mark.parametrize("d,T,n_grid", [(1, 33, 7), (2, 21, 14), (3, 22, 14), (4, 19, 10)])
+def test_grids_of_other_sizes_in_every_form(d, T, n_grid, dt):
+    forms.test_every_form_gives_the_same_scores(d, T, n_grid, dt)
 
 
 def test_more_series_than_a_split_launch_holds():
