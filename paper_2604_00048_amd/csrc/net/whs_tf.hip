@@ -956,6 +956,12 @@ __global__ __launch_bounds__(64 * W, W == 8 ? 4 : 3) void k_attn_bwd_kv(
   }
 }
 
+// Up to two workgroups of four wavefronts for each of the 256 CUs, that is what a call
+// beyond 128 rows takes, whatever the figures below say of more: it then spreads as far
+// as it goes (one series of 280 rows, forward, 8.0 us, with twelve wavefronts 11.6; two of
+// 4096 rows, forward and backward, 279, with eight 368; 48 of 600 rows 69 and 103).
+inline bool attn_few(int64_t P, int n) { return P * NH * ((n + 3) / 4) <= 512; }
+
 // Forward: whole multiples of four wavefronts, so that the SIMDs share the work.
 // Up to 384 rows one workgroup holds a whole (series, head) and up to 288 rows
 // arrive at once, so the wait for them comes once (4096 series of 280 rows: 0.34
@@ -966,7 +972,7 @@ enum AttnFwd { kShort, kMiddle, kLong };
 inline AttnFwd attn_fwd_shape(int64_t P, int T, dim3& grid, int& threads) {
   const int n = (T + ATN - 1) / ATN;
   const AttnFwd sh = n <= 4 ? kShort : n <= 12 ? kMiddle : kLong;
-  const int w = sh == kShort ? 4 : sh == kMiddle ? (n + 3) / 4 * 4 : 8;
+  const int w = sh == kShort || attn_few(P, n) ? 4 : sh == kMiddle ? (n + 3) / 4 * 4 : 8;
   threads = 64 * w;
   grid = dim3((unsigned)(P * NH * ((n + w - 1) / w)));
   return sh;
@@ -981,12 +987,12 @@ inline AttnFwd attn_fwd_shape(int64_t P, int T, dim3& grid, int& threads) {
 // the chip busy instead (64 series: 27 for 38 us).  Longer series as the forward.
 struct AttnBwd {
   unsigned grid;
-  int ch, rounds;
+  int waves, ch, rounds;
 };
 inline AttnBwd attn_bwd_shape(int64_t P, int T) {
-  const int n = (T + ATN - 1) / ATN, w = n <= 12 ? 4 : 8;
+  const int n = (T + ATN - 1) / ATN, w = n <= 12 || attn_few(P, n) ? 4 : 8;
   const int rounds = n <= 12 && P * NH >= 512 ? (n + w - 1) / w : 1, per = w * rounds;
-  return AttnBwd{(unsigned)(P * NH * ((n + per - 1) / per)), n <= 4 ? 128 : n <= 9 ? 288 : n <= 12 ? 384 : 0, rounds};
+  return AttnBwd{(unsigned)(P * NH * ((n + per - 1) / per)), w, n <= 4 ? 128 : n <= 9 ? 288 : n <= 12 ? 384 : 128, rounds};
 }
 
 template <int W, int CH>
@@ -1217,12 +1223,10 @@ int whs_tf_attn_bwd(const uint16_t* qkv, const uint16_t* o, const uint16_t* go, 
   if (!qkv || !o || !go || !lse || !dqkv || P < 0 || T < 1 || T > MAXT) return -1;
   if (P == 0) return 0;
   const AttnBwd a = attn_bwd_shape(P, T);
-  switch (a.ch) {
-    case 128: attn_bwd<4, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
-    case 288: attn_bwd<4, 288>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
-    case 384: attn_bwd<4, 384>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
-    default: attn_bwd<8, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv); break;
-  }
+  if (a.waves == 8) attn_bwd<8, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv);
+  else if (a.ch == 128) attn_bwd<4, 128>(a, hs(stream), qkv, o, go, lse, T, dqkv);
+  else if (a.ch == 288) attn_bwd<4, 288>(a, hs(stream), qkv, o, go, lse, T, dqkv);
+  else attn_bwd<4, 384>(a, hs(stream), qkv, o, go, lse, T, dqkv);
   return st(hipGetLastError());
 }
 
