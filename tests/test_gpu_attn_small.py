@@ -31,3 +31,17 @@ def test_batches_on_either_side_of_the_rule_agree(n, P, T):
     torch.cuda.synchronize()
     for small, large in zip(*out):
         assert torch.equal(large[:n], small)
+
+
+@pytest.mark.parametrize("P,T,bound", [(64, 40, 1.92e-7), (40, 500, 2.82e-7), (8, 1000, 3.07e-7)])
+def test_log_sum_exp_is_as_close_as_with_natural_exponents(P, T, bound):
+    """The root mean square error of the log-sum-exps against 64 bits; the bounds are those of
+    a kernel that keeps scores in units of e and rounds the scaled score once."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    qkv = torch.randn((P * T, 192), generator=g, device="cuda").bfloat16()
+    o = torch.empty((P * T, 64), dtype=torch.int16, device="cuda")
+    lse = torch.empty((P, 2, T), device="cuda")
+    tf.attn_fwd(qkv.view(torch.int16), P, T, o, lse)
+    q, k = (qkv[:, 64 * i:64 * i + 64].double().view(P, T, 2, 32).transpose(1, 2).contiguous() for i in (0, 1))
+    ref = torch.logsumexp((q @ k.transpose(-1, -2).contiguous()) / 32 ** 0.5, -1)
+    assert (lse.double() - ref).pow(2).mean().sqrt().item() <= bound
