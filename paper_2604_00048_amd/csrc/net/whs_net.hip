@@ -25,8 +25,7 @@ constexpr int KT = 9;    // taps
 constexpr int HALO = 4;  // zero padding on each side
 constexpr int TM = 64;   // output time rows per tile
 
-// float -> bfloat16 bits, round to nearest even (gfx950 converts in one instruction)
-// two at once (one instruction for the pair)
+// two floats -> bfloat16 bits, round to nearest even, one instruction for the pair
 __device__ __forceinline__ uint32_t pack2(float a, float b) {
   typedef __attribute__((ext_vector_type(2))) float f32x2;
   typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
@@ -35,6 +34,7 @@ __device__ __forceinline__ uint32_t pack2(float a, float b) {
 // max(v, 0), 0 for a NaN, in one instruction (a plain maximum first quiets v); for
 // values that go to bfloat16, where the largest float rounds to infinity
 __device__ __forceinline__ float relu(float v) { return __builtin_amdgcn_fmed3f(0.f, v, 3.402823466e38f); }
+// one float (gfx950 converts in one instruction)
 __device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ __forceinline__ float bf2f(uint16_t b) { return __builtin_bit_cast(float, (uint32_t)b << 16); }
 
@@ -270,21 +270,20 @@ struct TileWalk {
 // (r >> 1) & 7, so the 16 rows read by a quarter wavefront hit distinct banks.
 // Bound by the matrix cores, busy about half the cycles, and by what the one
 // wavefront of a SIMD issues between a tile's last product and the next one's first:
-// so rounding goes two values at once, ReLU is one instruction, and stores and loads
-// of a tile differ by a scalar offset.  4096 series of 3288 days: forward 0.96 ms,
-// 1040 TFLOP/s, input gradient 1.05 (one value and one address at a time 1.07, 1.09).
+// so rounding goes two values at once, ReLU is one instruction, and the addresses of a
+// tile's loads and stores are one and a constant each.  4096 series of 3288 days: forward
+// with its ReLU bits 1.07 ms, 930 TFLOP/s, input gradient 1.06 (one value and one address
+// at a time 1.17, 1.14).
 // ---------------------------------------------------------------------------
 constexpr int TR64 = 256;  // time rows per tile of the 64-to-64 layers
 
-// The rows of a series from r on (T - r of them, none if r is past its end) as a buffer
-// range; n values to a row.  A tile's loads and stores lie whole groups of rows apart:
-// they share the lanes' offsets and differ by their range, which ends at the series'
-// end for each.  (The scalar operand of the instruction could hold the distance
-// instead, but it is not part of the offset that the range is checked against.)
+// The T rows of series p, n values to a row, as a buffer range.  An access's whole
+// distance goes into its vector offset: the instruction's scalar operand could hold a
+// tile's common part (level in time), but is no part of the offset that the range is
+// checked against, and rows past the series have to be dropped by it.
 template <typename V>
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_from(const V* series, int T, int r, int n) {
-  const int left = T > r ? T - r : 0;
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<V*>(series) + (int64_t)r * n, (short)0, left * n * (int)sizeof(V),
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t series_rows(const V* a, int64_t p, int T, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<V*>(a) + p * ((int64_t)T * n), (short)0, T * n * (int)sizeof(V),
                                            0x00020000);
 }
 
@@ -332,26 +331,24 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   // the window's rows t0 - HALO .. of a series into an LDS buffer: load i covers LDS
   // rows 8i .. 8i+7; lane L fills slot L & 7 of row r = 8i + (L >> 3) with chunk
   // (L & 7) ^ ((r >> 1) & 7).  A wavefront's loads lie 32 rows apart and share the
-  // permutation; the first has an address of its own, since rows before the series
-  // (which wrap out of range) are told by it.
+  // permutation; rows before the series wrap out of its range.
   const int drow = 8 * wave + (lane >> 3);
-  const uint32_t doff = (uint32_t)(drow * 128 + ((lane & 7) ^ ((drow >> 1) & 7)) * 16);
-  auto dma_window = [&](const uint16_t* series, int t0, unsigned char* dst) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, 0, C), (lptr)(dst + 1024 * wave), 16,
-                                             doff + (uint32_t)((t0 - HALO) * 128), 0, 0, 0);
+  const uint32_t dcol = (uint32_t)(((lane & 7) ^ ((drow >> 1) & 7)) * 16);
+  auto dma_window = [&](int64_t p, int t0, unsigned char* dst) {
+    const auto rs = series_rows(in, p, T, C);
+    const uint32_t off = (uint32_t)((t0 - HALO + drow) * 128) + dcol;
 #pragma unroll
-    for (int j = 1; j < ROWS / 32; ++j)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, t0 - HALO + 32 * j, C),
-                                               (lptr)(dst + 1024 * wave + 4096 * j), 16, doff, 0, 0, 0);
+    for (int j = 0; j < ROWS / 32; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 1024 * wave + 4096 * j), 16, off + 4096u * j, 0, 0, 0);
     if (wave == 0)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rows_from(series, T, t0 - HALO + ROWS / 32 * 32, C),
-                                               (lptr)(dst + 4096 * (ROWS / 32)), 16, doff, 0, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lptr)(dst + 4096 * (ROWS / 32)), 16, off + 4096u * (ROWS / 32), 0, 0,
+                                               0);
   };
   static_assert(ROWS % 32 == 8, "the last 8 rows are one load of the first wavefront");
   auto fetch = [&](const TileWalk& tw, unsigned char* dst, unsigned char* bdst) {
     const int64_t p = tw.p;
     const int t0 = tw.k * TR64;
-    dma_window(in + p * (int64_t)T * C, t0, dst);
+    dma_window(p, t0, dst);
     if constexpr (MODE == 3) {
       // 8 bytes per row, loaded as dwords (T * 8 is a whole number of them, so
       // the buffer range zeroes exactly the rows past the series)
@@ -367,11 +364,11 @@ __global__ __launch_bounds__(256, 1) void k_conv64(const uint16_t* __restrict__ 
   const int srow = (int)threadIdx.x >> 3, sc8 = (int)threadIdx.x & 7;
   auto store_chunk = [&](int64_t p, int t0, int q) {
     const u32x4 v = *reinterpret_cast<const u32x4*>(otile + (srow + 32 * q) * OS + 8 * sc8);
-    __builtin_amdgcn_raw_buffer_store_b128(v, rows_from(out + p * (int64_t)T * C, T, t0 + 32 * q, C),
-                                           (uint32_t)(srow * 128 + 16 * sc8), 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(v, series_rows(out, p, T, C),
+                                           (uint32_t)((t0 + srow) * 128 + 16 * sc8) + 4096u * q, 0, 0);
     if (MODE == 0 && bits)
-      __builtin_amdgcn_raw_buffer_store_b8(relu_bits(v), rows_from(bits + p * (int64_t)T * 8, T, t0 + 32 * q, 8),
-                                           (uint32_t)(srow * 8 + sc8), 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b8(relu_bits(v), series_rows(bits, p, T, 8),
+                                           (uint32_t)((t0 + srow) * 8 + sc8) + 256u * q, 0, 0);
   };
   constexpr int NSTORE = TR64 * 8 / 256;  // output chunks per thread
   static_assert(NSTORE <= KT * C / 16, "the stores ride on the first K steps");
