@@ -44,7 +44,15 @@
  *   order t+1 is not positive definite: a non-positive or NaN weight, or too
  *   few observations); T when fewer than d samples are observed and rounding
  *   left every pivot positive (Omega is then singular for every weight).
- *   Outputs of a failed series are NaN; other series are unaffected.
+ *   Outputs of a failed series are NaN; other series are unaffected.  Where
+ *   Omega is singular to working precision (weights beyond about 1e6 on 3000
+ *   days with two or three observations, for instance) rounding decides
+ *   whether a pivot stays positive, and the order of elimination, which
+ *   depends on the call's layout, T and number of series, may decide it either
+ *   way; a series that loses only a pivot between two parts eliminated side by
+ *   side gets T as well.
+ * - Outputs may overlap an input only where the call says so below, and no
+ *   two outputs may overlap.
  */
 #ifndef WHS_H
 #define WHS_H
@@ -121,13 +129,17 @@ size_t whs_workspace_bytes(const whs_desc* desc);
  * and band count, and the uneven-date calls then accept interleave 1 too.
  * One band of d <= 2 in FP32, at least 96 steps long (512 for the solve with a
  * weight per series) on the daily grid, reads
- * and writes the contiguous arrays directly instead, several segments per
- * series, with the same results.
+ * and writes the contiguous arrays directly instead, in 2 to 32 segments per
+ * series up to 32,768 series and in one beyond.  The results are those of the
+ * interleaved call of the same series, bit for bit, copied or not.
  * With less (but at least whs_workspace_bytes), interleave-1 calls run the
  * kernels that read the contiguous layout in place: the same segments where
  * the workspace holds their checkpoints and P > 1024, else for one band and
  * d <= 2 the partition kernel (256 lanes per series, for P < 2^24), the faster
- * choice for the smallest batches. */
+ * choice for the smallest batches.  The segments' checkpoints can take up to
+ * 4 % more than whs_workspace_bytes for the adjoint of order 2 (3288 steps:
+ * from 2049 series on) and up to 17 % more at order 1; with exactly
+ * whs_workspace_bytes those calls run the partition kernel. */
 size_t whs_interleave_workspace_bytes(const whs_desc* desc);
 
 /* Bytes of the factor array whs_factor writes: P_pad * (d+1) * T * 8. */
@@ -317,6 +329,12 @@ int whs_variance(const whs_desc* desc, const uint8_t* w, const void* lambda, voi
  * is rescanned in time order).  whs_plan_lanes reports the lanes per series
  * of a group under the current configuration.  A plan is used by one stream
  * at a time.
+ *
+ * With one lane per series a group's z is that of whs_solve on the group, bit
+ * for bit, where whs_solve runs one lane per series too: FP64 storage, orders
+ * 3 and 4, more than 32,768 series, fewer than 96 steps, and one weight per
+ * series below 512 steps.  Elsewhere whs_solve eliminates several segments of
+ * a series side by side and the two differ by rounding.
  */
 typedef struct {
   int64_t n_series;  /* series in the group (>= 0)                   */

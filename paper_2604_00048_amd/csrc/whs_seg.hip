@@ -14,27 +14,30 @@ hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 // least 96 steps (4 tiles), and a batch that one lane per series leaves waiting on its
 // own recurrence.  3288 steps, order 2, a weight per difference row, solve /
 // adjoint in us, one lane per series -> segments:
-//      512 series   620 /  815 ->  48 /  69      16,384 series  681 / 869 -> 287 / 417
-//    4,096 series   643 /  825 -> 103 / 153      32,768 series  722 / 914 -> 558 / 801
+//      512 series   620 /  815 ->  48 /  69      16,384 series  681 / 869 -> 281 / 408
+//    4,096 series   643 /  825 -> 103 / 147      32,768 series  722 / 914 -> 558 / 801
 // (from 4096 series on the segments run at the memory's rate, about 28 and 40
 // bytes per series-step at 5 TB/s, checkpoints included).  512 steps, 4,096
 // series: 105 / 143 -> 22 / 29; 150 steps: 41 / 55 -> 17 / 22, 32,768 series 45 /
 // 58 -> 35 / 47; at 64 steps, three tiles, 34 / 41 -> 27 / 30 on 4,096 series but
 // level on 65,536 contiguous ones.  Ten bands, 16,384 series of 3288 steps: solve
-// and adjoint 8.07 -> 4.11 ms.  At 65,536 series one lane per series already
+// and adjoint 8.07 -> 4.16 ms.  At 65,536 series one lane per series already
 // fills every SIMD and moves fewer checkpoint bytes.
 // Series-contiguous arrays of one band take the same kernel, their row pieces
 // turned through LDS, instead of three copies into the interleaved layout and
-// back (or, for small batches, the partition kernel):
+// back (or, where the call's workspace has no room for copies, the partition kernel):
 //       64 series   611 /  812 ->  54 /  70      16,384 series   958 / 1315 ->  383 /  620
 //    4,096 series   706 /  951 -> 120 / 213      65,536 series  2091 / 3093 -> 1532 / 2484
-// (the last in one segment; interleaved, 103 / 146 and 281 / 393 at 4096 and 16,384: a lane's pieces of 88
+// (the last in one segment; slower than interleaved because a lane's pieces of 88
 // to 96 bytes split lines of 128, and the lines that 65,536 lanes hold open in
 // five arrays exceed the L2).
-// Not taken: FP64 storage, whose callers see the last digits, which another
-// order of elimination changes on ill-conditioned series; the one-band solve with
-// a weight per series below 512 steps, which gives bit for bit what a plan's
-// launch of one lane per series gives for that group; order 3 and 4, whose state leaves no registers for the spike.
+// Not taken: the one-band solve with a weight per series below 512 steps.  No
+// crossover lies there: segments would be ahead from 96 steps on (4,096 series of 365
+// steps 66 -> 16 us, of 511 89 -> 21; 32,768 of 511 92 -> 65).  It stays because a
+// plan's launch of one lane per series gives its groups bit for bit what this call
+// gives them, which is kept for groups of about a year, where it costs a call at most
+// some 70 us; longer ones, where it would cost up to 0.6 ms, agree to rounding.
+// Nor FP64 storage and orders 3 and 4, for which no segmented kernel has been built.
 // Several bands: the segments take 3 (solve) or 2 (adjoint) to a launch, one lane
 // per series 5 or 3 (solve) and 3, and every launch factors the series again.  With
 // eight segments and more that never matters; with fewer the segments' time grows
@@ -71,7 +74,8 @@ bool seg_path(const LaunchDesc& L, bool bwd) {
   if (L.S == 64) return L.C == 1 || bands_pay(L, bwd);
   // up to 1024 series the partition kernel's 256 lanes per series are ahead (64
   // series 25 / 27 us against 54 / 70, 1024 series 70 / 80 against 62 / 100); a
-  // call with the larger workspace keeps the interleaved call's results bit for bit
+  // call with the larger workspace keeps the interleaved call's results bit for bit,
+  // which the partition kernel does not give
   if (L.in_place && L.P <= 1024 && chunk_path(L)) return false;
   // a series-contiguous call's workspace is sized without the padding to whole workgroups
   const size_t need = L.D == 1 ? (bwd ? seg_contiguous_bytes<1, true>(L) : seg_contiguous_bytes<1, false>(L))
