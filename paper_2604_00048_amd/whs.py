@@ -191,8 +191,8 @@ def workspace_bytes(desc: WhsDesc) -> int:
 
 
 def _workspace(desc: WhsDesc, device, workspace, staged: bool = False):
-    """The caller's workspace (checked), or a new one; ``staged``: large enough for
-    series-contiguous calls to run the interleaved kernels on copies."""
+    """The caller's workspace (checked), or a new one; ``staged``: as large as
+    series-contiguous calls use, for interleaved copies where they make them."""
     n = workspace_bytes(desc)
     if workspace is not None:
         if workspace.numel() * workspace.element_size() < n:
@@ -256,9 +256,13 @@ def whs_solve(x: torch.Tensor, w: torch.Tensor, lam: torch.Tensor | None, d: int
     """``z = Omega^{-1} W x`` per series and band.  Returns ``(z, info)``.
 
     ``staged``: with interleave 1 and no workspace given, allocate the larger
-    workspace that lets the call run the interleaved kernels on copies
-    (``whs_interleave_workspace_bytes``); ``False`` keeps the kernels that read
-    the contiguous layout in place.
+    workspace (``whs_interleave_workspace_bytes``).  The call then gives the
+    interleaved call's results bit for bit: in place in segments for one band of
+    order <= 2 in float32 (daily grid, at least 96 steps; 512 for a solve with
+    one weight per series), else on interleaved copies.  ``False`` allocates
+    ``whs_workspace_bytes``, without room for copies: the partition kernel up to
+    1024 series (the fastest for them), beyond it the segments where that
+    workspace holds their checkpoints.
 
     ``coef``: rows of ``D`` on uneven sample times (``whs_diff_coef``); the
     daily grid when ``None``.
