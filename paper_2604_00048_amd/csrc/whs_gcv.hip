@@ -86,7 +86,8 @@ static hipError_t gcv_t(const GcvLaunch& L, hipStream_t stream) {
                                     : b.waves == 2 ? cu / 4 * 2 + (cu % 4 < 2 ? cu % 4 : 2)
                                                    : cu * ((b.waves + 3) / 4));
   if constexpr (D <= 2) {
-    if (5 * rounds * ((L.n_grid + 6) / 7) < 2 * turns) return gcv_go<D, TS, 7, 6, 64, 1, gcv_lone_tile<D, TS>()>(L, stream);
+    if (5 * rounds * ((L.n_grid + 6) / 7) < 2 * turns)
+      return gcv_go<D, TS, 7, 6, 64, 1, gcv_lone_tile<D, TS>()>(L, stream);
     return gcv_go<D, TS, G, 6, NT, 2>(L, stream);
   }
   return gcv_go<D, TS, G, 6, NT, 2>(L, stream, 7 * rounds * ((L.n_grid + G - 1) / G) < 6 * turns);

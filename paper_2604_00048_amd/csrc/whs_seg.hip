@@ -54,7 +54,8 @@ hipError_t run_seg_backward_d2(const LaunchDesc&, hipStream_t);
 //     adjoint  three bands, a weight per difference row 0.90-1.14, others 1.16-2.58
 static bool bands_pay(const LaunchDesc& L, bool bwd) {
   SegShape s;
-  if (bwd ? !seg_shape<seg_tile<2, 2, true, true>()>(L, s) : !seg_shape<seg_tile<2, 2, false, true>()>(L, s)) return false;
+  if (bwd ? !seg_shape<seg_tile<2, 2, true, true>()>(L, s) : !seg_shape<seg_tile<2, 2, false, true>()>(L, s))
+    return false;
   if (s.nseg > 4) return true;
   const int widest = seg_group(L.C, bwd), one_lane = max_group(L.D, bwd, false, L.perdiff);
   const int n = (L.C + widest - 1) / widest, n1 = (L.C + one_lane - 1) / one_lane;
